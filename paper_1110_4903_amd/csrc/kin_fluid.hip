@@ -6,7 +6,7 @@
 //
 // A step is dimensionally split: an x sweep then a y sweep (or the reverse).  A sweep is three
 // Runge-Kutta stages (the strong-stability-preserving third-order scheme), and a stage is three
-// kernels, each bound by HBM bandwidth:
+// kernels:
 //   fluid_prim    per cell: Q -> primitive W = (rho_s, u, v, P) and T (Newton on the energy,
 //                 from the cell's previous T), with P from Dalton's law (Sec. 2, Eq. dalton);
 //   fluid_flux    per face: MP5 left and right states of every primitive variable (Sec. 3.1,
@@ -17,7 +17,13 @@
 // One thread per cell or face; consecutive threads take consecutive x, so every array access
 // of a wavefront is one or two contiguous runs of a row.  The face kernel reads its six-cell
 // stencil from the primitive array, which neighbouring threads share through the caches.
-// Species are streamed (three passes per face), so no per-species array lives in registers.
+//
+// The face kernel is bound by FP64 issue and the latency of its loads, the others by memory.  On a
+// 1024 x 1024 grid of nine species the faces of a stage took 110 us with a division and branches in
+// each limiter, a selection of every coefficient per lane and the energies summed species by species
+// (2130 VALU instructions per wavefront); they take 58-82 us as written here, the updates that also
+// form primitives 73-100 us.  100250 cells of 36 species: 95 us to 38-50 us for the faces, 102 us
+// to 30 us for those updates, whose Newton summed over the species in every iteration.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -28,45 +34,36 @@
 namespace kin {
 namespace {
 
-constexpr double kRuJ = 8.31446261815324e3;   // J/(kmol K): R / M with M in g/mol gives J/(kg K)
 constexpr double kAlphaMP = 2.0;
-// Species counts whose face states and densities the kernels keep in registers, in two classes:
-// the arrays are sized by the class, so a small mixture in the larger class would hold registers
-// for species it does not have (the 9-species mixture's face kernel: 118 VGPRs and four
-// wavefronts per SIMD in the small class, 142 and three in the larger).
-constexpr int kFluidNsSmall = 10;
+// Mixtures of at most this many species run kernels compiled for their species count: face states
+// and densities stay in registers, and the species loops unroll without a test between them, so the
+// loads of one species are not held back until the previous one is done.  Larger mixtures stream
+// their species (NSR = 0).
 constexpr int kFluidNsRegs = 16;
 
-__device__ __forceinline__ double minmod(double a, double b)
-{
-    return (a * b > 0.0) ? (a > 0.0 ? fmin(a, b) : fmax(a, b)) : 0.0;
-}
+// median(0, a, b): zero when the signs differ, else the argument of smaller magnitude
+__device__ __forceinline__ double minmod(double a, double b) { return fmax(fmin(a, b), fmin(fmax(a, b), 0.0)); }
 
 // Left state of the face j + 1/2 from cells j-2..j+2 (Eq. mp5), limited by the median with u_j
 // and u_j + minmod(u_{j+1} - u_j, alpha (u_j - u_{j-1})) (Eqs. mp, ump); the right state is the
-// same function of the mirrored stencil.
+// same function of the mirrored stencil.  The bound is itself a median, of u_j, u_{j+1} and
+// u_j + alpha (u_j - u_{j-1}), so the whole limiter is minima and maxima: 18 FP64 instructions
+// and no division (the branching form with a division by 60 took about 40).  A value that is not
+// a number in any of the five cells reaches the result through uL.
 __device__ __forceinline__ double mp5(double um2, double um1, double u0, double up1, double up2)
 {
-    const double uL = (2.0 * um2 - 13.0 * um1 + 47.0 * u0 + 27.0 * up1 - 3.0 * up2) / 60.0;
-    const double ump = u0 + minmod(up1 - u0, kAlphaMP * (u0 - um1));
+    const double uL = fma(up2, -3.0 / 60.0, fma(up1, 27.0 / 60.0, fma(u0, 47.0 / 60.0, fma(um1, -13.0 / 60.0, um2 * (2.0 / 60.0)))));
+    const double far = fma(kAlphaMP, u0 - um1, u0);
+    const double ump = fmax(fmin(u0, up1), fmin(fmax(u0, up1), far));
     return uL + minmod(u0 - uL, ump - uL);
 }
 
-// Sensible energy e_s(T) - e_s(T_ref) (J/kg) and c_v,s (J/(kg K)) of species s.  The species
-// index is uniform across the wavefront, so both coefficient ranges come through scalar loads
-// and each lane selects its range.
-__device__ __forceinline__ void species_e_cv(const WaveTables &t, int s, double T, double &e, double &cv)
+// 1/x from the hardware reciprocal refined by two Newton steps (within an ulp for normal x)
+__device__ __forceinline__ double recip(double x)
 {
-    const auto *nasa = uniform_table(t.nasa) + 14 * s;
-    const bool lo = T < uniform_table(t.Tmid)[s];
-    double a[6];
-#pragma unroll
-    for (int k = 0; k < 6; ++k) a[k] = lo ? nasa[k] : nasa[7 + k];
-    const double Rs = kRuJ / uniform_table(t.M)[s];
-    const double cpR = fma(T, fma(T, fma(T, fma(T, a[4], a[3]), a[2]), a[1]), a[0]);
-    const double hR = fma(T, fma(T, fma(T, fma(T, fma(T, a[4] * 0.2, a[3] * 0.25), a[2] * (1.0 / 3.0)), a[1] * 0.5), a[0]), a[5]);
-    e = Rs * (hR - T) - uniform_table(t.ef)[s];
-    cv = Rs * (cpR - 1.0);
+    double y = __builtin_amdgcn_rcp(x);
+    y = fma(y, fma(-x, y, 1.0), y);
+    return fma(y, fma(-x, y, 1.0), y);
 }
 
 struct Grid {
@@ -74,89 +71,111 @@ struct Grid {
     long long n;          // nx * ny
 };
 
+// body(s) for every species: unrolled for a compile-time count, else a loop of four at a time
+template <int NSR, typename Body>
+__device__ __forceinline__ void each_species(int ns, Body body)
+{
+    if constexpr (NSR > 0) {
+#pragma unroll
+        for (int s = 0; s < NSR; ++s) body(s);
+    } else {
+#pragma unroll 4
+        for (int s = 0; s < ns; ++s) body(s);
+    }
+}
+
+// Coefficients of the mixture's energy as a polynomial in T: with each species' energy
+// e_s(T) = sum_k E_sk T^k (fluid table), B_k = sum_s rho_s E_sk gives sum_s rho_s e_s = sum B_k T^k
+// and rho c_v = sum k B_k T^(k-1), for one choice of NASA-7 range per species.  The species index
+// is uniform, so the coefficients come through scalar loads; a wavefront whose lanes all lie above
+// (or all below) every species' switch temperature reads one range and selects nothing.
+template <int NSR, typename Dens>
+__device__ __forceinline__ void mix_coefs(const WaveTables &t, int ns, double T, Dens dens, double (&B)[6])
+{
+#pragma unroll
+    for (int k = 0; k < 6; ++k) B[k] = 0.0;
+    const auto *fl = uniform_table(t.fl);
+    auto one_range = [&](int o) {
+        each_species<NSR>(ns, [&](int s) {
+            const double r = dens(s);
+#pragma unroll
+            for (int k = 0; k < 6; ++k) B[k] = fma(r, fl[kFluidTab * s + o + k], B[k]);
+        });
+    };
+    if (__all(T >= t.Tsw_hi)) {
+        one_range(6);
+    } else if (__all(T < t.Tsw_lo)) {
+        one_range(0);
+    } else {
+        each_species<NSR>(ns, [&](int s) {
+            const double r = dens(s);
+            const bool lo = T < fl[kFluidTab * s + 13];
+#pragma unroll
+            for (int k = 0; k < 6; ++k) B[k] = fma(r, lo ? fl[kFluidTab * s + k] : fl[kFluidTab * s + 6 + k], B[k]);
+        });
+    }
+}
+
+__device__ __forceinline__ double mix_energy(const double (&B)[6], double T)
+{
+    return fma(T, fma(T, fma(T, fma(T, fma(T, B[5], B[4]), B[3]), B[2]), B[1]), B[0]);
+}
+
+__device__ __forceinline__ double mix_cv(const double (&B)[6], double T)
+{
+    return fma(T, fma(T, fma(T, fma(T, 5.0 * B[5], 4.0 * B[4]), 3.0 * B[3]), 2.0 * B[2]), B[1]);
+}
+
 // Primitive variables of cell i from its conserved state q (ns partial densities, two momenta,
 // E; q(v) returns variable v): u, v, P = rho R T into W's last three rows and T into Tc, by
 // Newton on the sensible energy from the cell's previous T.  The partial densities are W's
 // species rows by definition, so the face kernel reads them from the state itself.
-// NSR > 0: the partial densities stay in registers through the Newton iterations (mechanisms
-// of at most NSR species); NSR = 0 reads them through q again in each iteration.
+// Within one choice of NASA-7 range per species the mixture's energy is a polynomial, whose
+// coefficients are summed once per choice: an iteration evaluates one polynomial, and the sums are
+// redone only when T leaves the interval between switch temperatures that they hold for.
 template <int NSR, typename QV>
 __device__ __forceinline__ void cell_primitives(const WaveTables &t, const Grid &g, long long i, QV q, double *W,
                                                 double *Tc)
 {
-    const int ns = g.ns;
+    const int ns = NSR > 0 ? NSR : g.ns;
     const long long n = g.n;
-    double rs[NSR > 0 ? NSR : 1];
-    auto each_species = [&](auto body) {
-        if constexpr (NSR > 0) {
-#pragma unroll
-            for (int s = 0; s < NSR; ++s)
-                if (s < ns) body(s);
-        } else {
-            for (int s = 0; s < ns; ++s) body(s);
-        }
-    };
-    auto rho_s = [&](int s) { return NSR > 0 ? rs[s] : q(s); };
+    const auto *fl = uniform_table(t.fl);
     double rho = 0.0, rR = 0.0;
-    each_species([&](int s) {
+    each_species<NSR>(ns, [&](int s) {
         const double r = q(s);
-        if constexpr (NSR > 0) rs[s] = r;
         rho += r;
-        rR = fma(r, kRuJ / uniform_table(t.M)[s], rR);
+        rR = fma(r, fl[kFluidTab * s + 12], rR);
     });
-    const double u = q(ns) / rho, v = q(ns + 1) / rho;
+    const double ir = 1.0 / rho;
+    const double u = q(ns) * ir, v = q(ns + 1) * ir;
     const double eint = q(ns + 2) - 0.5 * rho * (u * u + v * v);
     double T = Tc[i];
     if (!(T >= 100.0 && T <= 1e4)) T = 1000.0;
-    if constexpr (NSR > 0) {
-        // Within one choice of NASA-7 range per species the mixture's sensible energy is itself
-        // a polynomial in T: with w_s = rho_s R_s and B_k = sum_s w_s a_sk, sum_s rho_s e_s(T) =
-        // B_5 + T (B_0 + T (B_1 / 2 + ... + T B_4 / 5)) - rR T - sum_s rho_s ef_s, and the heat
-        // capacity is B_0 + T (B_1 + ... + T B_4) - rR.  The B_k are summed once per range choice
-        // (a bit per species, set below its switch temperature), so a Newton iteration costs one
-        // polynomial instead of one per species.
-        static_assert(NSR <= 32, "range mask");
-        double B[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, EF = 0.0;
-        each_species([&](int s) { EF = fma(rs[s], uniform_table(t.ef)[s], EF); });
-        unsigned used = ~0u;  // no valid choice yet (ns <= 16 < 32 bits)
-        for (int it = 0; it < 60; ++it) {
-            unsigned lo = 0;
-            each_species([&](int s) { lo |= (T < uniform_table(t.Tmid)[s] ? 1u : 0u) << s; });
-            if (lo != used) {
-                used = lo;
-#pragma unroll
-                for (int k = 0; k < 6; ++k) B[k] = 0.0;
-                each_species([&](int s) {
-                    const auto *nasa = uniform_table(t.nasa) + 14 * s;
-                    const bool l = (lo >> s) & 1u;
-                    const double w = rs[s] * (kRuJ / uniform_table(t.M)[s]);
-#pragma unroll
-                    for (int k = 0; k < 6; ++k) B[k] = fma(w, l ? nasa[k] : nasa[7 + k], B[k]);
+    double B[6];
+    double lo = 1.0, hi = 0.0;   // B holds for lo <= T < hi (at first for nothing)
+    bool go = true;
+    for (int it = 0; it < 60 && go; ++it) {
+        if (!(T >= lo && T < hi)) {
+            mix_coefs<NSR>(t, ns, T, q, B);
+            if (T >= t.Tsw_hi) {
+                lo = t.Tsw_hi;
+                hi = __builtin_inf();
+            } else if (T < t.Tsw_lo) {
+                lo = -__builtin_inf();
+                hi = t.Tsw_lo;
+            } else {
+                lo = -__builtin_inf();
+                hi = __builtin_inf();
+                each_species<NSR>(ns, [&](int s) {
+                    const double m = fl[kFluidTab * s + 13];
+                    if (T < m) hi = fmin(hi, m);
+                    else lo = fmax(lo, m);
                 });
             }
-            const double C = fma(T, fma(T, fma(T, fma(T, B[4], B[3]), B[2]), B[1]), B[0]);
-            const double H = fma(T, fma(T, fma(T, fma(T, fma(T, B[4] * 0.2, B[3] * 0.25), B[2] * (1.0 / 3.0)),
-                                                B[1] * 0.5), B[0]), B[5]);
-            const double f = H - rR * T - EF - eint;
-            const double d = C - rR;
-            const double dT = f / d;
-            T -= dT;
-            if (!(fabs(dT) > 1e-13 * fabs(T))) break;   // converged, or not a number
         }
-    } else {
-        for (int it = 0; it < 60; ++it) {
-            double f = -eint, d = 0.0;
-            each_species([&](int s) {
-                double e, cv;
-                species_e_cv(t, s, T, e, cv);
-                const double r = rho_s(s);
-                f = fma(r, e, f);
-                d = fma(r, cv, d);
-            });
-            const double dT = f / d;
-            T -= dT;
-            if (!(fabs(dT) > 1e-13 * fabs(T))) break;   // converged, or not a number
-        }
+        const double dT = (mix_energy(B, T) - eint) * recip(mix_cv(B, T));
+        T -= dT;
+        go = fabs(dT) > 1e-13 * fabs(T);   // until converged, or not a number
     }
     Tc[i] = T;
     W[(size_t)ns * n + i] = u;
@@ -165,12 +184,19 @@ __device__ __forceinline__ void cell_primitives(const WaveTables &t, const Grid 
 }
 
 template <int NSR>
-__global__ void fluid_prim_kernel(WaveTables t, Grid g, const double *Q, double *W, double *Tc)
+__global__ void __launch_bounds__(256) fluid_prim_kernel(WaveTables t, Grid g, const double *Q, double *W, double *Tc)
 {
     const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= g.n) return;
     const long long n = g.n;
-    cell_primitives<NSR>(t, g, i, [&](int v) { return Q[(size_t)v * n + i]; }, W, Tc);
+    if constexpr (NSR > 0) {
+        double q[NSR + 3];
+#pragma unroll
+        for (int v = 0; v < NSR + 3; ++v) q[v] = Q[(size_t)v * n + i];
+        cell_primitives<NSR>(t, g, i, [&](int v) { return q[v]; }, W, Tc);
+    } else {
+        cell_primitives<0>(t, g, i, [&](int v) { return Q[(size_t)v * n + i]; }, W, Tc);
+    }
 }
 
 // Cell index along the sweep direction k (0..len-1 after the boundary rule) of an offset one.
@@ -180,22 +206,35 @@ __device__ __forceinline__ int wrap(int k, int len, int bc)
     return k < 0 ? 0 : (k >= len ? len - 1 : k);
 }
 
-// Face fluxes of a sweep along x (DIR 0) or y (DIR 1).  Face a along the sweep lies between
-// cells a - 1 and a; faces are stored [var][ny][nx + 1] (x) or [var][ny + 1][nx] (y).
-// NSR > 0: mechanisms of at most NSR species keep each species' two reconstructed states in
-// registers (one reconstruction per species); NSR = 0 streams them (three per species).
-template <int DIR, int NSR>
-__global__ void __launch_bounds__(256) fluid_flux_kernel(WaveTables t, Grid g, const double *Qs, const double *W, double *F)
+// sqrt of a positive number from the hardware's reciprocal square root and two coupled Newton
+// steps (within an ulp), zero for zero
+__device__ __forceinline__ double sqrt_pos(double x)
 {
-    const long long f = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const int fw = DIR == 0 ? g.nx + 1 : g.nx;      // faces per row of the face array
-    const int fh = DIR == 0 ? g.ny : g.ny + 1;
-    if (f >= (long long)fw * fh) return;
-    const int fx = (int)(f % fw), fy = (int)(f / fw);
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+    const double r = fma(-h, g, 0.5);
+    g = fma(g, r, g);
+    h = fma(h, r, h);
+    g = fma(fma(-g, g, x), h, g);
+    return x == 0.0 ? 0.0 : g;
+}
+
+// Face fluxes of a sweep along x (DIR 0) or y (DIR 1).  Face a along the sweep lies between
+// cells a - 1 and a.  put(v, F) receives the flux of variable v.
+// NSR > 0: each species is reconstructed once and both of its states stay in registers; NSR = 0
+// reconstructs it again in each pass over the species (three, or two where every species has one
+// NASA-7 range, whose energies do not wait for the temperature).
+// The HLLE flux of a variable is, with w_L = b+ / (b+ - b-), w_R = -b- / (b+ - b-) and
+// p = b+ b- / (b+ - b-), w_L F_L + w_R F_R + p (Q_R - Q_L); every F is Q u_n plus a pressure term,
+// so each variable's flux is Q_L (w_L u_L - p) + Q_R (w_R u_R + p) and the pressure's share.
+template <int DIR, int NSR, typename Put>
+__device__ __forceinline__ void face_flux(const WaveTables &t, const Grid &g, int fx, int fy, const double *Qs,
+                                          const double *W, Put put)
+{
     const int a = DIR == 0 ? fx : fy;                 // face index along the sweep
     const int len = DIR == 0 ? g.nx : g.ny;
     const long long n = g.n;
-    const int ns = g.ns;
+    const int ns = NSR > 0 ? NSR : g.ns;
     // cells a-3 .. a+2 along the sweep (j = a - 1 is the face's left cell)
     long long c[6];
 #pragma unroll
@@ -214,86 +253,116 @@ __global__ void __launch_bounds__(256) fluid_flux_kernel(WaveTables t, Grid g, c
     recon(Wun, unL, unR);
     recon(Wut, utL, utR);
     recon(W + (size_t)(ns + 2) * n, PL, PR);
-    // species states: reconstructed once into registers (NSR), or again in each pass below
-    double Ls[NSR > 0 ? NSR : 1], Rsv[NSR > 0 ? NSR : 1];
-    if (NSR > 0) {
+    double Ls[NSR > 0 ? NSR : 1], Rv[NSR > 0 ? NSR : 1];
+    if constexpr (NSR > 0) {
 #pragma unroll
-        for (int s = 0; s < (NSR > 0 ? NSR : 1); ++s)
-            if (s < ns) recon(Qs + (size_t)s * n, Ls[s], Rsv[s]);
+        for (int s = 0; s < NSR; ++s) recon(Qs + (size_t)s * n, Ls[s], Rv[s]);
     }
     auto state = [&](int s, double &L, double &R) {
-        if (NSR > 0) {
+        if constexpr (NSR > 0) {
             L = Ls[s];
-            R = Rsv[s];
+            R = Rv[s];
         } else {
             recon(Qs + (size_t)s * n, L, R);
         }
     };
-    // body(s) for every species: unrolled over the register arrays, or a plain loop
-    auto each_species = [&](auto body) {
-        if constexpr (NSR > 0) {
+    // densities, gas constants and temperatures of the two states, then their energies and heat
+    // capacities (one side after the other: six coefficients are live at a time)
+    const auto *fl = uniform_table(t.fl);
+    double rL = 0.0, rR = 0.0, GL = 0.0, GR = 0.0, BL[6], BR[6], TL, TR;
+    if constexpr (NSR > 0) {
+        each_species<NSR>(ns, [&](int s) {
+            const double Rs = fl[kFluidTab * s + 12];
+            rL += Ls[s];
+            rR += Rv[s];
+            GL = fma(Ls[s], Rs, GL);
+            GR = fma(Rv[s], Rs, GR);
+        });
+        TL = PL * recip(GL);
+        TR = PR * recip(GR);
+        mix_coefs<NSR>(t, ns, TL, [&](int s) { return Ls[s]; }, BL);
+    } else {
+        const bool one = t.Tsw_hi <= 0.0;   // one range for every species
 #pragma unroll
-            for (int s = 0; s < NSR; ++s)
-                if (s < ns) body(s);
-        } else {
-            for (int s = 0; s < ns; ++s) body(s);
-        }
-    };
-    // pass 1: densities and gas constants of the two states
-    double rL = 0.0, rR = 0.0, RL = 0.0, RR = 0.0;
-    each_species([&](int s) {
-        double L, R;
-        state(s, L, R);
-        const double Rs = kRuJ / uniform_table(t.M)[s];
-        rL += L;
-        rR += R;
-        RL = fma(L, Rs, RL);
-        RR = fma(R, Rs, RR);
-    });
-    const double TL = PL / RL, TR = PR / RR;
-    // pass 2: energies and heat capacities at the two temperatures
-    double eL = 0.0, eR = 0.0, cvL = 0.0, cvR = 0.0;
-    each_species([&](int s) {
-        double L, R, e, cv;
-        state(s, L, R);
-        species_e_cv(t, s, TL, e, cv);
-        eL = fma(L, e, eL);
-        cvL = fma(L, cv, cvL);
-        species_e_cv(t, s, TR, e, cv);
-        eR = fma(R, e, eR);
-        cvR = fma(R, cv, cvR);
-    });
+        for (int k = 0; k < 6; ++k) BL[k] = BR[k] = 0.0;
+        auto add = [&](int s, double L, double R, bool loL, bool loR) {
+#pragma unroll
+            for (int k = 0; k < 6; ++k) {
+                const double lo = fl[kFluidTab * s + k], hi = fl[kFluidTab * s + 6 + k];
+                BL[k] = fma(L, loL ? lo : hi, BL[k]);
+                BR[k] = fma(R, loR ? lo : hi, BR[k]);
+            }
+        };
+        auto sums = [&](auto with_energy) {
+            each_species<0>(ns, [&](int s) {
+                double L, R;
+                state(s, L, R);
+                const double Rs = fl[kFluidTab * s + 12];
+                rL += L;
+                rR += R;
+                GL = fma(L, Rs, GL);
+                GR = fma(R, Rs, GR);
+                if constexpr (decltype(with_energy)::value) add(s, L, R, false, false);
+            });
+        };
+        if (one) sums(std::true_type{});
+        else sums(std::false_type{});
+        TL = PL * recip(GL);
+        TR = PR * recip(GR);
+        if (!one)
+            each_species<0>(ns, [&](int s) {
+                double L, R;
+                state(s, L, R);
+                const double m = fl[kFluidTab * s + 13];
+                add(s, L, R, TL < m, TR < m);
+            });
+    }
+    const double eL = mix_energy(BL, TL), cvL = mix_cv(BL, TL);
+    if constexpr (NSR > 0) mix_coefs<NSR>(t, ns, TR, [&](int s) { return Rv[s]; }, BR);
+    const double eR = mix_energy(BR, TR), cvR = mix_cv(BR, TR);
     const double EL = eL + 0.5 * rL * (unL * unL + utL * utL);
     const double ER = eR + 0.5 * rR * (unR * unR + utR * utR);
-    const double cL = sqrt((cvL + RL) / cvL * PL / rL), cR = sqrt((cvR + RR) / cvR * PR / rR);
-    const double sL = sqrt(rL), sR = sqrt(rR);
-    const double uh = (sL * unL + sR * unR) / (sL + sR);
-    const double c2h = (sL * cL * cL + sR * cR * cR) / (sL + sR) +
-                       0.5 * sL * sR / ((sL + sR) * (sL + sR)) * (unR - unL) * (unR - unL);
-    const double ch = sqrt(c2h);
+    const double c2L = (cvL + GL) * PL * recip(cvL * rL), c2R = (cvR + GR) * PR * recip(cvR * rR);
+    const double cL = sqrt_pos(c2L), cR = sqrt_pos(c2R);
+    const double sL = sqrt_pos(rL), sR = sqrt_pos(rR);
+    const double is = recip(sL + sR), du = unR - unL;
+    const double uh = (sL * unL + sR * unR) * is;
+    const double c2h = (sL * c2L + sR * c2R) * is + 0.5 * (sL * is) * (sR * is) * (du * du);
+    const double ch = sqrt_pos(c2h);
     const double bp = fmax(0.0, fmax(uh + ch, unR + cR));
     const double bm = fmin(0.0, fmin(uh - ch, unL - cL));
-    const double idb = 1.0 / (bp - bm), pm = bp * bm * idb;
-    auto hlle = [&](double FL, double FR, double QL, double QR) { return (bp * FL - bm * FR) * idb + pm * (QR - QL); };
-    const long long fo = DIR == 0 ? (long long)fy * (g.nx + 1) + fx : (long long)fy * g.nx + fx;
-    const long long fn = (long long)fw * fh;
-    // pass 3: species fluxes
-    each_species([&](int s) {
+    const double idb = recip(bp - bm);
+    const double wL = bp * idb, wR = -bm * idb, pm = wL * bm;
+    const double aL = fma(wL, unL, -pm), aR = fma(wR, unR, pm);
+    const double pP = fma(wL, PL, wR * PR);
+    each_species<NSR>(ns, [&](int s) {
         double L, R;
         state(s, L, R);
-        F[(size_t)s * fn + fo] = hlle(L * unL, R * unR, L, R);
+        put(s, fma(L, aL, R * aR));
     });
-    F[(size_t)(DIR == 0 ? ns : ns + 1) * fn + fo] =
-        hlle(rL * unL * unL + PL, rR * unR * unR + PR, rL * unL, rR * unR);
-    F[(size_t)(DIR == 0 ? ns + 1 : ns) * fn + fo] = hlle(rL * unL * utL, rR * unR * utR, rL * utL, rR * utR);
-    F[(size_t)(ns + 2) * fn + fo] = hlle(unL * (EL + PL), unR * (ER + PR), EL, ER);
+    const double mL = rL * aL, mR = rR * aR;
+    put(DIR == 0 ? ns : ns + 1, fma(mL, unL, fma(mR, unR, pP)));
+    put(DIR == 0 ? ns + 1 : ns, fma(mL, utL, mR * utR));
+    put(ns + 2, fma(EL, aL, fma(ER, aR, fma(wL * unL, PL, wR * unR * PR))));
+}
+
+// Faces are stored [var][ny][nx + 1] (x) or [var][ny + 1][nx] (y).
+template <int DIR, int NSR>
+__global__ void __launch_bounds__(256) fluid_flux_kernel(WaveTables t, Grid g, const double *Qs, const double *W, double *F)
+{
+    const long long f = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const int fw = DIR == 0 ? g.nx + 1 : g.nx;      // faces per row of the face array
+    const int fh = DIR == 0 ? g.ny : g.ny + 1;
+    const long long fn = (long long)fw * fh;
+    if (f >= fn) return;
+    face_flux<DIR, NSR>(t, g, (int)(f % fw), (int)(f / fw), Qs, W, [&](int v, double x) { F[(size_t)v * fn + f] = x; });
 }
 
 // Qout = a0 Q0 + a1 (Q + dt L), L = -(F_{a+1} - F_a) / h (in place allowed: each thread reads
-// and writes only its own cell).
+// and writes only its own cell).  r = dt / h.
 template <int DIR>
 __global__ void fluid_update_kernel(Grid g, const double *Q0, const double *Q, double *Qout, const double *F,
-                                    double dt, double h, double a0, double a1)
+                                    double r, double a0, double a1)
 {
     const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= g.n) return;
@@ -302,9 +371,9 @@ __global__ void fluid_update_kernel(Grid g, const double *Q0, const double *Q, d
     const long long fn = DIR == 0 ? (long long)(g.nx + 1) * g.ny : (long long)g.nx * (g.ny + 1);
     const long long fl = DIR == 0 ? (long long)y * (g.nx + 1) + x : i;
     const long long fr = DIR == 0 ? fl + 1 : fl + g.nx;
+#pragma unroll 4
     for (int v = 0; v < nv; ++v) {
-        const double L = -(F[(size_t)v * fn + fr] - F[(size_t)v * fn + fl]) / h;
-        const double q = Q[(size_t)v * g.n + i] + dt * L;
+        const double q = fma(r, F[(size_t)v * fn + fl] - F[(size_t)v * fn + fr], Q[(size_t)v * g.n + i]);
         Qout[(size_t)v * g.n + i] = a0 != 0.0 ? a0 * Q0[(size_t)v * g.n + i] + a1 * q : a1 * q;
     }
 }
@@ -312,36 +381,30 @@ __global__ void fluid_update_kernel(Grid g, const double *Q0, const double *Q, d
 // The update of fluid_update_kernel, then the primitives of the new state for the next stage
 // (the new state stays in registers, so it is not read back).
 template <int DIR, int NSR>
-__global__ void fluid_update_prim_kernel(WaveTables t, Grid g, const double *Q0, const double *Q, double *Qout,
-                                         const double *F, double dt, double h, double a0, double a1, double *W,
-                                         double *Tc)
+__global__ void __launch_bounds__(256) fluid_update_prim_kernel(WaveTables t, Grid g, const double *Q0, const double *Q,
+                                                                double *Qout, const double *F, double r, double a0,
+                                                                double a1, double *W, double *Tc)
 {
     const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= g.n) return;
     const int x = (int)(i % g.nx), y = (int)(i / g.nx);
-    const int nv = g.ns + 3;
     const long long fn = DIR == 0 ? (long long)(g.nx + 1) * g.ny : (long long)g.nx * (g.ny + 1);
     const long long fl = DIR == 0 ? (long long)y * (g.nx + 1) + x : i;
     const long long fr = DIR == 0 ? fl + 1 : fl + g.nx;
-    constexpr int NV = NSR > 0 ? NSR + 3 : 1;
-    double qn[NV];
     auto upd = [&](int v) {
-        const double L = -(F[(size_t)v * fn + fr] - F[(size_t)v * fn + fl]) / h;
-        const double q = Q[(size_t)v * g.n + i] + dt * L;
+        const double q = fma(r, F[(size_t)v * fn + fl] - F[(size_t)v * fn + fr], Q[(size_t)v * g.n + i]);
         const double o = a0 != 0.0 ? a0 * Q0[(size_t)v * g.n + i] + a1 * q : a1 * q;
         Qout[(size_t)v * g.n + i] = o;
         return o;
     };
     if constexpr (NSR > 0) {
+        double qn[NSR + 3];
 #pragma unroll
-        for (int k = 0; k < NV; ++k) {
-            // species k < ns, then the momenta and the energy in slots NSR .. NSR + 2
-            const int v = k < NSR ? k : g.ns + (k - NSR);
-            if (k < NSR && k >= g.ns) continue;
-            qn[k] = upd(v);
-        }
-        cell_primitives<NSR>(t, g, i, [&](int v) { return v < g.ns ? qn[v] : qn[NSR + (v - g.ns)]; }, W, Tc);
+        for (int v = 0; v < NSR + 3; ++v) qn[v] = upd(v);
+        cell_primitives<NSR>(t, g, i, [&](int v) { return qn[v]; }, W, Tc);
     } else {
+        const int nv = g.ns + 3;
+#pragma unroll 4
         for (int v = 0; v < nv; ++v) upd(v);
         const long long n = g.n;
         cell_primitives<0>(t, g, i, [&](int v) { return Qout[(size_t)v * n + i]; }, W, Tc);
@@ -363,16 +426,16 @@ __global__ void __launch_bounds__(kSpeedThreads) fluid_speed_kernel(WaveTables t
     for (long long i = (long long)blockIdx.x * kSpeedThreads + threadIdx.x; i < g.n;
          i += (long long)gridDim.x * kSpeedThreads) {
         const long long n = g.n;
-        double rho = 0.0, rR = 0.0, cv = 0.0;
+        double rho = 0.0, rR = 0.0, B[6];
         const double T = Tc[i];
-        for (int s = 0; s < g.ns; ++s) {
+        const auto *fl = uniform_table(t.fl);
+        mix_coefs<0>(t, g.ns, T, [&](int s) {
             const double rs = Q[(size_t)s * n + i];
-            double e, cvs;
-            species_e_cv(t, s, T, e, cvs);
             rho += rs;
-            rR = fma(rs, kRuJ / t.M[s], rR);
-            cv = fma(rs, cvs, cv);
-        }
+            rR = fma(rs, fl[kFluidTab * s + 12], rR);
+            return rs;
+        }, B);
+        const double cv = mix_cv(B, T);
         const double P = W[(size_t)(g.ns + 2) * n + i];
         const double c = sqrt((cv + rR) / cv * P / rho);
         double ri = fmax((fabs(W[(size_t)g.ns * n + i]) + c) / dx, (fabs(W[(size_t)(g.ns + 1) * n + i]) + c) / dy);
@@ -411,13 +474,13 @@ __global__ void fluid_energy_back_kernel(Grid g, double *Q, const double *KE, co
     Q[(size_t)(g.ns + 2) * g.n + i] = Es[i] + KE[i];
 }
 
-// f(std::integral_constant<int, NSR>) with the register class of ns species (0: streamed).
-template <typename Fn>
+// f(std::integral_constant<int, NSR>): the species count itself up to kFluidNsRegs, else 0 (streamed)
+template <int NSR = 1, typename Fn>
 void ns_class(int ns, Fn f)
 {
-    if (ns <= kFluidNsSmall) f(std::integral_constant<int, kFluidNsSmall>{});
-    else if (ns <= kFluidNsRegs) f(std::integral_constant<int, kFluidNsRegs>{});
-    else f(std::integral_constant<int, 0>{});
+    if constexpr (NSR > kFluidNsRegs) f(std::integral_constant<int, 0>{});
+    else if (ns == NSR) f(std::integral_constant<int, NSR>{});
+    else ns_class<NSR + 1>(ns, f);
 }
 
 }  // namespace
@@ -442,11 +505,11 @@ hipError_t launch_fluid_sweep(const WaveTables &t, const FluidGrid &fg, int dir,
             constexpr int D = decltype(dirc)::value;
             hipLaunchKernelGGL((fluid_flux_kernel<D, NSR>), dim3(gf), dim3(block), 0, s, t, g, in, W, F);
             if (k == 2)
-                hipLaunchKernelGGL(fluid_update_kernel<D>, dim3(gc), dim3(block), 0, s, g, Q, in, out, F, dt, h, a0[k],
+                hipLaunchKernelGGL(fluid_update_kernel<D>, dim3(gc), dim3(block), 0, s, g, Q, in, out, F, dt / h, a0[k],
                                    a1[k]);
             else
                 hipLaunchKernelGGL((fluid_update_prim_kernel<D, NSR>), dim3(gc), dim3(block), 0, s, t, g, Q, in, out, F,
-                                   dt, h, a0[k], a1[k], W, T);
+                                   dt / h, a0[k], a1[k], W, T);
         };
         for (int k = 0; k < 3; ++k) {
             const double *in = k == 0 ? Q : Q1;

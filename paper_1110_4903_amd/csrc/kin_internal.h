@@ -75,6 +75,7 @@ namespace kin {
 
 // Mechanism tables in device memory, read by the table-driven kernels (wave layout and the
 // initial-energy kernel).  All pointers point into one allocation.
+constexpr int kFluidTab = 16;   // values per species of the fluid table
 constexpr int kChunk = 64;   // reactions evaluated per wavefront pass
 
 // Compact reaction record (48 bytes).  A reaction has six species slots: reactants in slots
@@ -114,6 +115,11 @@ struct WaveTables {
     const double *rxd;      // [nr][4]: ln A, b, Ta, sum nu
     const RxnRec *rxc;      // [nr]
     const RxnCoef *rxk;     // [nr]
+    // fluid kernels: per species kFluidTab values, the energy e_s(T) - e_s(T_ref) (J/kg) as a
+    // polynomial sum_k E_k T^k below (0..5) and above (6..11) its switch temperature, then R_s
+    // (J/(kg K)) and the switch temperature (a species whose two ranges agree has none: 0)
+    const double *fl;
+    double Tsw_lo, Tsw_hi;  // smallest and largest switch temperature (0 where no species has one)
     const double *ef;       // [ns] e_s(T_ref) at T_ref = 298.15 K, J/kg (conserved-variable adapter)
     const double *effT;     // [ns][ntb] third-body efficiencies per slot, transposed
     const double *tbA;      // [ceil(ntb/4)][ceil(ns/16)][64] nu_qs M_s in matrix-operand tiles

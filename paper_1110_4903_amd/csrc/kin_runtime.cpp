@@ -430,6 +430,24 @@ static kin_status upload_tables(kin_ctx *ctx, Mech &m)
         const double h_RT = a[0] + Tr * (a[1] / 2 + Tr * (a[2] / 3 + Tr * (a[3] / 4 + Tr * a[4] / 5))) + a[5] / Tr;
         ef[s] = 8.31446261815324e3 / h.M[s] * Tr * (h_RT - 1.0);
     }
+    // fluid table: e_s(T) - e_s(T_ref) = R_s (a_5 + (a_0 - 1) T + a_1 T^2 / 2 + ... + a_4 T^5 / 5) - e_s(T_ref)
+    std::vector<double> fl((size_t)kFluidTab * ns, 0.0);
+    double Tsw_lo = 0.0, Tsw_hi = 0.0;
+    for (int s = 0; s < ns; ++s) {
+        double *p = &fl[(size_t)kFluidTab * s];
+        const double Rs = 8.31446261815324e3 / h.M[s];
+        for (int q = 0; q < 2; ++q) {
+            const double *a = &h.nasa[(size_t)14 * s + 7 * q];
+            p[6 * q] = Rs * a[5] - ef[s];
+            p[6 * q + 1] = Rs * (a[0] - 1.0);
+            for (int k = 1; k < 5; ++k) p[6 * q + 1 + k] = Rs * a[k] / (k + 1);
+        }
+        p[12] = Rs;
+        if (h.single_range(s)) continue;
+        p[13] = h.Tmid[s];
+        Tsw_lo = Tsw_hi == 0.0 ? h.Tmid[s] : std::min(Tsw_lo, h.Tmid[s]);
+        Tsw_hi = std::max(Tsw_hi, h.Tmid[s]);
+    }
     // dense third-body terms as a small matrix product per cell: J[s][k] += sum_q A[s][q] B[q][k]
     // with A[s][q] = nu_qs M_s D_q (D_q = q_f - q_b of slot q, known only in the kernel) and
     // B[q][k] = eff_qk / M_k.  tbA holds nu_qs M_s and tbB holds B, both cut into the operand
@@ -497,7 +515,8 @@ static kin_status upload_tables(kin_ctx *ctx, Mech &m)
         {effT.data(), sizeof(double) * effT.size(), 0}, {tbA.data(), sizeof(double) * tbA.size(), 0},
         {tbB.data(), sizeof(double) * tbB.size(), 0}, {chunk_rp.data(), sizeof(int) * chunk_rp.size(), 0},
         {ef.data(), sizeof(double) * ns, 0}, {tgs.data(), sizeof(int) * tgs.size(), 0},
-        {tgf.data(), sizeof(double) * tgf.size(), 0}, {effTM.data(), sizeof(double) * effTM.size(), 0}};
+        {tgf.data(), sizeof(double) * tgf.size(), 0}, {effTM.data(), sizeof(double) * effTM.size(), 0},
+        {fl.data(), sizeof(double) * fl.size(), 0}};
     size_t total = 0;
     for (Piece &p : pc) { p.off = total; total = align256(total + p.bytes); }
     std::vector<char> host(total, 0);
@@ -509,6 +528,8 @@ static kin_status upload_tables(kin_ctx *ctx, Mech &m)
     WaveTables &t = m.tab;
     t.ns = ns; t.nr = nr; t.ntb = ntb; t.nchunk = nchunk; t.ntbe = ntbe;
     t.tb_last = tb_last;
+    t.Tsw_lo = Tsw_lo; t.Tsw_hi = Tsw_hi;
+    t.fl = reinterpret_cast<const double *>(b + pc[14].off);
     t.lnPaR = std::log(kPatmCgs / kRuCgs);
     t.nasa = reinterpret_cast<const double *>(b + pc[0].off);
     t.Tmid = reinterpret_cast<const double *>(b + pc[1].off);

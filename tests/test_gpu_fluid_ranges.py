@@ -1,0 +1,76 @@
+"""GPU parity of the fluid step for mixtures whose species switch NASA-7 range at temperatures of
+their own, inside the flow's range: wavefronts whose lanes lie above every switch, below every switch
+or on both sides, at species counts around the compiled ones (up to 16) and streamed (17 and up).
+Gate: 1e-10 of each conserved variable's scale, as for the other fluid parity tests (two steps of
+FP64 arithmetic in another order: some 1e3 roundings of 1e-16 at most)."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+from paper_1110_4903_amd import synth
+from tests.test_gpu_fluid import flow_state, scaled_diff
+
+pytestmark = pytest.mark.gpu
+
+
+def two_range(ns, seed):
+    """A generated mixture whose species, but every fourth, have a second range: cp/R larger by 0.2 to 1
+    above 900-1300 K, with h and s continuous there."""
+    m = synth.make_mechanism(synth.MechRecipe("two%d" % ns, seed=seed, n_elements=4 if ns > 20 else 3, n_species=ns,
+                                              n_reactions=3 * ns,
+                                              frac_third_body=0.15, frac_irreversible=0.3))
+    rng = np.random.default_rng(seed)
+    nasa, Tm = m.nasa.copy(), rng.uniform(900.0, 1300.0, ns)
+    for s in range(ns):
+        if s % 4 == 3:
+            continue
+        d = rng.uniform(0.2, 1.0)
+        nasa[s, 1, 0] += d
+        nasa[s, 1, 5] -= d * Tm[s]
+        nasa[s, 1, 6] -= d * np.log(Tm[s])
+    return dataclasses.replace(m, nasa=nasa, T_mid=Tm)
+
+
+@pytest.mark.parametrize("ns,bc,T", [(5, 1, (500.0, 1800.0)), (16, 0, (500.0, 1800.0)), (17, 1, (500.0, 1800.0)),
+                                     (40, 0, (500.0, 1800.0)), (9, 0, (400.0, 850.0)), (9, 1, (1400.0, 2500.0))])
+def test_fluid_steps_two_ranges(ns, bc, T):
+    from oracle import fluid_oracle as fo
+    from paper_1110_4903_amd import kin
+    m = two_range(ns, 40 + ns)
+    gas = fo.Gas(m)
+    nx, ny = 70, 17   # more than a wavefront along x, ragged both ways
+    dx, dy = 1e-3 / nx, 1e-3 / ny
+    Q = flow_state(fo, gas, nx, ny, ns, *T)
+    with kin.Context(0) as ctx:
+        mid = ctx.mech_upload(m)
+        fid = ctx.fluid_create(mid, nx, ny, dx, dy, bc)
+        ctx.fluid_upload(fid, np.ascontiguousarray(Q))
+        dt = fo.max_dt(gas, Q, dx, dy, 0.4)
+        assert abs(ctx.fluid_max_dt(fid, 0.4) - dt) <= 1e-12 * dt
+        Qo = Q
+        for k in range(2):
+            ctx.fluid_step(fid, dt, y_first=bool(k))
+            Qo = fo.fluid_step(gas, Qo, dt, dx, dy, "outflow" if bc else "periodic", y_first=bool(k))
+        d = scaled_diff(ctx.fluid_download(fid), Qo)
+        assert np.all(d <= 1e-10), d
+
+
+def test_fluid_invalid_cell_stays_visible():
+    """A cell that is not a number makes the step size zero, and spreads to its neighbours' states
+    instead of being clipped away by the limiter."""
+    from oracle import fluid_oracle as fo
+    from paper_1110_4903_amd import kin
+    m = synth.mechanism("mech9")
+    gas = fo.Gas(m)
+    nx, ny = 33, 21
+    Q = np.ascontiguousarray(flow_state(fo, gas, nx, ny, 3))
+    Q[2, 10, 16] = np.nan
+    with kin.Context(0) as ctx:
+        fid = ctx.fluid_create(ctx.mech_upload(m), nx, ny, 1e-4, 1e-4, 0)
+        ctx.fluid_upload(fid, Q)
+        assert ctx.fluid_max_dt(fid, 0.4) == 0.0
+        ctx.fluid_step(fid, 1e-9)
+        bad = ~np.isfinite(ctx.fluid_download(fid)).all(0)
+        # three stages of a three-cell stencil each way: the sweeps' rows and columns
+        assert bad[10, 16] and bad[10, 13:20].all() and bad[7:14, 16].all() and not bad[:, :5].any()
