@@ -5,25 +5,32 @@
 // chemistry sub-step of the split (the conserved-variable adapter) uses the same energy.
 //
 // A step is dimensionally split: an x sweep then a y sweep (or the reverse).  A sweep is three
-// Runge-Kutta stages (the strong-stability-preserving third-order scheme), and a stage is three
-// kernels:
-//   fluid_prim    per cell: Q -> primitive W = (rho_s, u, v, P) and T (Newton on the energy,
-//                 from the cell's previous T), with P from Dalton's law (Sec. 2, Eq. dalton);
-//   fluid_flux    per face: MP5 left and right states of every primitive variable (Sec. 3.1,
-//                 Eq. mp5) with the monotonicity-preserving bound (Eqs. mp, ump), and the HLLE
-//                 flux between them (Eq. fluxhlle);
-//   fluid_update  per cell: the stage's combination of the sweep's start state, the stage state
-//                 and dt times the flux difference.
-// One thread per cell or face; consecutive threads take consecutive x, so every array access
-// of a wavefront is one or two contiguous runs of a row.  The face kernel reads its six-cell
-// stencil from the primitive array, which neighbouring threads share through the caches.
+// Runge-Kutta stages (the strong-stability-preserving third-order scheme).  A stage is
+//   primitives   per cell: Q -> W = (u, v, P) and T (Newton on the energy, from the cell's previous
+//                T), with P from Dalton's law (Sec. 2, Eq. dalton); rho_s are primitives already;
+//   fluxes       per face: MP5 left and right states of every primitive variable (Sec. 3.1,
+//                Eq. mp5) with the monotonicity-preserving bound (Eqs. mp, ump), and the HLLE
+//                flux between them (Eq. fluxhlle);
+//   update       per cell: the stage's combination of the sweep's start state, the stage state
+//                and dt times the flux difference.
+// Up to 16 species one kernel does a stage: a cell's two fluxes, its update and the primitives of
+// its new state stay in registers (fluid_stage_x_kernel, fluid_stage_y_kernel), and only the step's
+// first primitives have a kernel of their own.  Larger mixtures do a stage in two kernels, with the
+// fluxes in memory.  One thread per cell or face; consecutive threads take consecutive x, so every
+// array access of a wavefront is one or two contiguous runs of a row.  The six-cell stencil is read
+// from the state and primitive arrays, which neighbouring threads share through the caches.
 //
-// The face kernel is bound by FP64 issue and the latency of its loads, the others by memory.  On a
-// 1024 x 1024 grid of nine species the faces of a stage took 110 us with a division and branches in
-// each limiter, a selection of every coefficient per lane and the energies summed species by species
-// (2130 VALU instructions per wavefront); they take 58-82 us as written here, the updates that also
-// form primitives 73-100 us.  100250 cells of 36 species: 95 us to 38-50 us for the faces, 102 us
-// to 30 us for those updates, whose Newton summed over the species in every iteration.
+// What bounds it: a fused stage of nine species on 1024 x 1024 cells takes 113 us along x and 143 us
+// along y, where its 352 bytes a cell at the rate of a large copy (4.7 TB/s) would take 79 us; two
+// wavefronts per SIMD (about 210 and 240 registers: the six-cell loads of nine species in flight)
+// hide the rest of the latency incompletely, and a bound on the registers makes the compiler spill
+// (2.8 ms a step with three wavefronts).  A step takes 1.58 ms; 1.93 ms with the fluxes in memory (a
+// stage's faces 58-82 us, its update with primitives 73-100 us), 2.33 ms when also each limiter had a
+// division and branches, every coefficient was selected per lane and the energies were summed species
+// by species.  3750 cells: 135 us, 182 us and 323 us, of which the fused form saves launches and the
+// update its test on a0 per variable, which put each variable's loads behind the last one's.
+// 100250 cells of 36 species: 0.93 ms, from 2.22 ms whose Newton summed over the species in every
+// iteration.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -71,6 +78,21 @@ struct Grid {
     long long n;          // nx * ny
 };
 
+// Byte offset of a cell in an array.  The kernels of a compiled species count use 32 bits (a grid whose
+// arrays reach 4 GiB each takes the streamed ones): an access is then a scalar base, which holds the
+// variable, and one offset register for all of a cell's variables, instead of a 64-bit address each.
+template <int NSR> using Off = std::conditional_t<(NSR > 0), unsigned, unsigned long long>;
+template <typename O>
+__device__ __forceinline__ double ld(const double *base, O off)
+{
+    return *reinterpret_cast<const double *>(reinterpret_cast<const char *>(base) + off);
+}
+template <typename O>
+__device__ __forceinline__ void st(double *base, O off, double v)
+{
+    *reinterpret_cast<double *>(reinterpret_cast<char *>(base) + off) = v;
+}
+
 // body(s) for every species: unrolled for a compile-time count, else a loop of four at a time
 template <int NSR, typename Body>
 __device__ __forceinline__ void each_species(int ns, Body body)
@@ -89,31 +111,41 @@ __device__ __forceinline__ void each_species(int ns, Body body)
 // and rho c_v = sum k B_k T^(k-1), for one choice of NASA-7 range per species.  The species index
 // is uniform, so the coefficients come through scalar loads; a wavefront whose lanes all lie above
 // (or all below) every species' switch temperature reads one range and selects nothing.
-template <int NSR, typename Dens>
-__device__ __forceinline__ void mix_coefs(const WaveTables &t, int ns, double T, Dens dens, double (&B)[6])
+// Species s has row row(s) of the table.
+template <int NSR, typename Dens, typename Row>
+__device__ __forceinline__ void mix_coefs(const WaveTables &t, int ns, double T, Dens dens, Row row, double (&B)[6])
 {
 #pragma unroll
     for (int k = 0; k < 6; ++k) B[k] = 0.0;
-    const auto *fl = uniform_table(t.fl);
-    auto one_range = [&](int o) {
+    auto one_range = [&](int o, auto share) {   // o = 0 or 6
+        // a pointer of its own in each path: the compiler would load what two paths share before the
+        // branch, and hold a hundred coefficients in registers across it
+        const double *p = t.fl;
+        asm volatile("" : "+s"(p));
+        const auto *fl = uniform_table(p);
         each_species<NSR>(ns, [&](int s) {
-            const double r = dens(s);
+            const double r = share(s, dens(s));
 #pragma unroll
-            for (int k = 0; k < 6; ++k) B[k] = fma(r, fl[kFluidTab * s + o + k], B[k]);
+            for (int k = 0; k < 6; ++k) B[k] = fma(r, fl[kFluidTab * row(s) + o + k], B[k]);
         });
     };
-    if (__all(T >= t.Tsw_hi)) {
-        one_range(6);
-    } else if (__all(T < t.Tsw_lo)) {
-        one_range(0);
+    auto all = [](int, double r) { return r; };
+    const int mode = __builtin_amdgcn_readfirstlane(__all(T >= t.Tsw_hi) ? 2 : (__all(T < t.Tsw_lo) ? 0 : 1));
+    if (mode != 1) {
+        one_range(3 * mode, all);
     } else {
-        each_species<NSR>(ns, [&](int s) {
-            const double r = dens(s);
-            const bool lo = T < fl[kFluidTab * s + 13];
-#pragma unroll
-            for (int k = 0; k < 6; ++k) B[k] = fma(r, lo ? fl[kFluidTab * s + k] : fl[kFluidTab * s + 6 + k], B[k]);
-        });
+        // each range with the densities of the species that it holds for (a selection of coefficients would
+        // become a load per lane), one range after the other
+        const auto *sw = uniform_table(t.fl) + 13;
+        one_range(0, [&](int s, double r) { return T < sw[kFluidTab * row(s)] ? r : 0.0; });
+        one_range(6, [&](int s, double r) { return T < sw[kFluidTab * row(s)] ? 0.0 : r; });
     }
+}
+
+template <int NSR, typename Dens>
+__device__ __forceinline__ void mix_coefs(const WaveTables &t, int ns, double T, Dens dens, double (&B)[6])
+{
+    mix_coefs<NSR>(t, ns, T, dens, [](int s) { return s; }, B);
 }
 
 __device__ __forceinline__ double mix_energy(const double (&B)[6], double T)
@@ -126,15 +158,35 @@ __device__ __forceinline__ double mix_cv(const double (&B)[6], double T)
     return fma(T, fma(T, fma(T, fma(T, 5.0 * B[5], 4.0 * B[4]), 3.0 * B[3]), 2.0 * B[2]), B[1]);
 }
 
+// The temperatures lo <= T' < hi at which every species has the NASA-7 range that it has at T
+template <int NSR>
+__device__ __forceinline__ void range_interval(const WaveTables &t, int ns, double T, double &lo, double &hi)
+{
+    lo = -__builtin_inf();
+    hi = __builtin_inf();
+    if (T >= t.Tsw_hi) {
+        lo = t.Tsw_hi;
+    } else if (T < t.Tsw_lo) {
+        hi = t.Tsw_lo;
+    } else {
+        const auto *fl = uniform_table(t.fl);
+        each_species<NSR>(ns, [&](int s) {
+            const double m = fl[kFluidTab * s + 13];
+            if (T < m) hi = fmin(hi, m);
+            else lo = fmax(lo, m);
+        });
+    }
+}
+
 // Primitive variables of cell i from its conserved state q (ns partial densities, two momenta,
-// E; q(v) returns variable v): u, v, P = rho R T into W's last three rows and T into Tc, by
-// Newton on the sensible energy from the cell's previous T.  The partial densities are W's
-// species rows by definition, so the face kernel reads them from the state itself.
+// E; q(v) returns variable v): u, v, P = rho R T into the three rows of W and T into Tc, by
+// Newton on the sensible energy from the cell's previous T.  The partial densities are primitives
+// as they are, so the face kernel reads them from the state itself.
 // Within one choice of NASA-7 range per species the mixture's energy is a polynomial, whose
 // coefficients are summed once per choice: an iteration evaluates one polynomial, and the sums are
 // redone only when T leaves the interval between switch temperatures that they hold for.
 template <int NSR, typename QV>
-__device__ __forceinline__ void cell_primitives(const WaveTables &t, const Grid &g, long long i, QV q, double *W,
+__device__ __forceinline__ void cell_primitives(const WaveTables &t, const Grid &g, Off<NSR> o, QV q, double *W,
                                                 double *Tc)
 {
     const int ns = NSR > 0 ? NSR : g.ns;
@@ -149,7 +201,7 @@ __device__ __forceinline__ void cell_primitives(const WaveTables &t, const Grid 
     const double ir = 1.0 / rho;
     const double u = q(ns) * ir, v = q(ns + 1) * ir;
     const double eint = q(ns + 2) - 0.5 * rho * (u * u + v * v);
-    double T = Tc[i];
+    double T = ld(Tc, o);
     if (!(T >= 100.0 && T <= 1e4)) T = 1000.0;
     double B[6];
     double lo = 1.0, hi = 0.0;   // B holds for lo <= T < hi (at first for nothing)
@@ -157,30 +209,16 @@ __device__ __forceinline__ void cell_primitives(const WaveTables &t, const Grid 
     for (int it = 0; it < 60 && go; ++it) {
         if (!(T >= lo && T < hi)) {
             mix_coefs<NSR>(t, ns, T, q, B);
-            if (T >= t.Tsw_hi) {
-                lo = t.Tsw_hi;
-                hi = __builtin_inf();
-            } else if (T < t.Tsw_lo) {
-                lo = -__builtin_inf();
-                hi = t.Tsw_lo;
-            } else {
-                lo = -__builtin_inf();
-                hi = __builtin_inf();
-                each_species<NSR>(ns, [&](int s) {
-                    const double m = fl[kFluidTab * s + 13];
-                    if (T < m) hi = fmin(hi, m);
-                    else lo = fmax(lo, m);
-                });
-            }
+            range_interval<NSR>(t, ns, T, lo, hi);
         }
         const double dT = (mix_energy(B, T) - eint) * recip(mix_cv(B, T));
         T -= dT;
         go = fabs(dT) > 1e-13 * fabs(T);   // until converged, or not a number
     }
-    Tc[i] = T;
-    W[(size_t)ns * n + i] = u;
-    W[(size_t)(ns + 1) * n + i] = v;
-    W[(size_t)(ns + 2) * n + i] = rR * T;
+    st(Tc, o, T);
+    st(W, o, u);
+    st(W + n, o, v);
+    st(W + 2 * n, o, rR * T);
 }
 
 template <int NSR>
@@ -190,12 +228,13 @@ __global__ void __launch_bounds__(256) fluid_prim_kernel(WaveTables t, Grid g, c
     if (i >= g.n) return;
     const long long n = g.n;
     if constexpr (NSR > 0) {
+        const Off<NSR> o = 8u * (unsigned)i;
         double q[NSR + 3];
 #pragma unroll
-        for (int v = 0; v < NSR + 3; ++v) q[v] = Q[(size_t)v * n + i];
-        cell_primitives<NSR>(t, g, i, [&](int v) { return q[v]; }, W, Tc);
+        for (int v = 0; v < NSR + 3; ++v) q[v] = ld(Q + (size_t)v * n, o);
+        cell_primitives<NSR>(t, g, o, [&](int v) { return q[v]; }, W, Tc);
     } else {
-        cell_primitives<0>(t, g, i, [&](int v) { return Q[(size_t)v * n + i]; }, W, Tc);
+        cell_primitives<0>(t, g, 8ull * i, [&](int v) { return Q[(size_t)v * n + i]; }, W, Tc);
     }
 }
 
@@ -219,14 +258,42 @@ __device__ __forceinline__ double sqrt_pos(double x)
     return x == 0.0 ? 0.0 : g;
 }
 
+// The HLLE flux of a variable is, with w_L = b+ / (b+ - b-), w_R = -b- / (b+ - b-) and
+// p = b+ b- / (b+ - b-), w_L F_L + w_R F_R + p (Q_R - Q_L); every F is Q u_n plus a pressure term,
+// so each variable's flux is Q_L (w_L u_L - p) + Q_R (w_R u_R + p) and the pressure's share.
+struct Hlle {
+    double aL, aR, un, ut, E;   // a species' flux is its L aL + R aR; fluxes of momentum and energy
+};
+
+// From the states' velocities, pressures, densities, gas constants rho R, energies and heat capacities.
+__device__ __forceinline__ Hlle hlle(double unL, double unR, double utL, double utR, double PL, double PR, double rL, double rR,
+                                     double GL, double GR, double eL, double eR, double cvL, double cvR)
+{
+    const double EL = eL + 0.5 * rL * (unL * unL + utL * utL);
+    const double ER = eR + 0.5 * rR * (unR * unR + utR * utR);
+    const double c2L = (cvL + GL) * PL * recip(cvL * rL), c2R = (cvR + GR) * PR * recip(cvR * rR);
+    const double cL = sqrt_pos(c2L), cR = sqrt_pos(c2R);
+    const double sL = sqrt_pos(rL), sR = sqrt_pos(rR);
+    const double is = recip(sL + sR), du = unR - unL;
+    const double uh = (sL * unL + sR * unR) * is;
+    const double c2h = (sL * c2L + sR * c2R) * is + 0.5 * (sL * is) * (sR * is) * (du * du);
+    const double ch = sqrt_pos(c2h);
+    const double bp = fmax(0.0, fmax(uh + ch, unR + cR));
+    const double bm = fmin(0.0, fmin(uh - ch, unL - cL));
+    const double idb = recip(bp - bm);
+    const double wL = bp * idb, wR = -bm * idb, pm = wL * bm;
+    const double aL = fma(wL, unL, -pm), aR = fma(wR, unR, pm);
+    const double pP = fma(wL, PL, wR * PR);
+    const double mL = rL * aL, mR = rR * aR;
+    return {aL, aR, fma(mL, unL, fma(mR, unR, pP)), fma(mL, utL, mR * utR),
+            fma(EL, aL, fma(ER, aR, fma(wL * unL, PL, wR * unR * PR)))};
+}
+
 // Face fluxes of a sweep along x (DIR 0) or y (DIR 1).  Face a along the sweep lies between
 // cells a - 1 and a.  put(v, F) receives the flux of variable v.
 // NSR > 0: each species is reconstructed once and both of its states stay in registers; NSR = 0
 // reconstructs it again in each pass over the species (three, or two where every species has one
 // NASA-7 range, whose energies do not wait for the temperature).
-// The HLLE flux of a variable is, with w_L = b+ / (b+ - b-), w_R = -b- / (b+ - b-) and
-// p = b+ b- / (b+ - b-), w_L F_L + w_R F_R + p (Q_R - Q_L); every F is Q u_n plus a pressure term,
-// so each variable's flux is Q_L (w_L u_L - p) + Q_R (w_R u_R + p) and the pressure's share.
 template <int DIR, int NSR, typename Put>
 __device__ __forceinline__ void face_flux(const WaveTables &t, const Grid &g, int fx, int fy, const double *Qs,
                                           const double *W, Put put)
@@ -236,23 +303,23 @@ __device__ __forceinline__ void face_flux(const WaveTables &t, const Grid &g, in
     const long long n = g.n;
     const int ns = NSR > 0 ? NSR : g.ns;
     // cells a-3 .. a+2 along the sweep (j = a - 1 is the face's left cell)
-    long long c[6];
+    Off<NSR> c[6];
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
         const int q = wrap(a - 3 + k, len, g.bc);
-        c[k] = DIR == 0 ? (long long)fy * g.nx + q : (long long)q * g.nx + fx;
+        c[k] = 8 * (DIR == 0 ? (Off<NSR>)fy * g.nx + q : (Off<NSR>)q * g.nx + fx);
     }
     auto recon = [&](const double *w, double &L, double &R) {
-        const double v0 = w[c[0]], v1 = w[c[1]], v2 = w[c[2]], v3 = w[c[3]], v4 = w[c[4]], v5 = w[c[5]];
+        const double v0 = ld(w, c[0]), v1 = ld(w, c[1]), v2 = ld(w, c[2]), v3 = ld(w, c[3]), v4 = ld(w, c[4]), v5 = ld(w, c[5]);
         L = mp5(v0, v1, v2, v3, v4);
         R = mp5(v5, v4, v3, v2, v1);
     };
-    const double *Wun = W + (size_t)(DIR == 0 ? ns : ns + 1) * n;
-    const double *Wut = W + (size_t)(DIR == 0 ? ns + 1 : ns) * n;
+    const double *Wun = W + (size_t)(DIR == 0 ? 0 : 1) * n;
+    const double *Wut = W + (size_t)(DIR == 0 ? 1 : 0) * n;
     double unL, unR, utL, utR, PL, PR;
     recon(Wun, unL, unR);
     recon(Wut, utL, utR);
-    recon(W + (size_t)(ns + 2) * n, PL, PR);
+    recon(W + (size_t)2 * n, PL, PR);
     double Ls[NSR > 0 ? NSR : 1], Rv[NSR > 0 ? NSR : 1];
     if constexpr (NSR > 0) {
 #pragma unroll
@@ -286,11 +353,19 @@ __device__ __forceinline__ void face_flux(const WaveTables &t, const Grid &g, in
 #pragma unroll
         for (int k = 0; k < 6; ++k) BL[k] = BR[k] = 0.0;
         auto add = [&](int s, double L, double R, bool loL, bool loR) {
+            const double Ll = loL ? L : 0.0, Lh = loL ? 0.0 : L, Rl = loR ? R : 0.0, Rh = loR ? 0.0 : R;
 #pragma unroll
             for (int k = 0; k < 6; ++k) {
                 const double lo = fl[kFluidTab * s + k], hi = fl[kFluidTab * s + 6 + k];
-                BL[k] = fma(L, loL ? lo : hi, BL[k]);
-                BR[k] = fma(R, loR ? lo : hi, BR[k]);
+                BL[k] = fma(Ll, lo, fma(Lh, hi, BL[k]));
+                BR[k] = fma(Rl, lo, fma(Rh, hi, BR[k]));
+            }
+        };
+        auto add_hi = [&](int s, double L, double R) {
+#pragma unroll
+            for (int k = 0; k < 6; ++k) {
+                BL[k] = fma(L, fl[kFluidTab * s + 6 + k], BL[k]);
+                BR[k] = fma(R, fl[kFluidTab * s + 6 + k], BR[k]);
             }
         };
         auto sums = [&](auto with_energy) {
@@ -302,7 +377,7 @@ __device__ __forceinline__ void face_flux(const WaveTables &t, const Grid &g, in
                 rR += R;
                 GL = fma(L, Rs, GL);
                 GR = fma(R, Rs, GR);
-                if constexpr (decltype(with_energy)::value) add(s, L, R, false, false);
+                if constexpr (decltype(with_energy)::value) add_hi(s, L, R);
             });
         };
         if (one) sums(std::true_type{});
@@ -320,34 +395,19 @@ __device__ __forceinline__ void face_flux(const WaveTables &t, const Grid &g, in
     const double eL = mix_energy(BL, TL), cvL = mix_cv(BL, TL);
     if constexpr (NSR > 0) mix_coefs<NSR>(t, ns, TR, [&](int s) { return Rv[s]; }, BR);
     const double eR = mix_energy(BR, TR), cvR = mix_cv(BR, TR);
-    const double EL = eL + 0.5 * rL * (unL * unL + utL * utL);
-    const double ER = eR + 0.5 * rR * (unR * unR + utR * utR);
-    const double c2L = (cvL + GL) * PL * recip(cvL * rL), c2R = (cvR + GR) * PR * recip(cvR * rR);
-    const double cL = sqrt_pos(c2L), cR = sqrt_pos(c2R);
-    const double sL = sqrt_pos(rL), sR = sqrt_pos(rR);
-    const double is = recip(sL + sR), du = unR - unL;
-    const double uh = (sL * unL + sR * unR) * is;
-    const double c2h = (sL * c2L + sR * c2R) * is + 0.5 * (sL * is) * (sR * is) * (du * du);
-    const double ch = sqrt_pos(c2h);
-    const double bp = fmax(0.0, fmax(uh + ch, unR + cR));
-    const double bm = fmin(0.0, fmin(uh - ch, unL - cL));
-    const double idb = recip(bp - bm);
-    const double wL = bp * idb, wR = -bm * idb, pm = wL * bm;
-    const double aL = fma(wL, unL, -pm), aR = fma(wR, unR, pm);
-    const double pP = fma(wL, PL, wR * PR);
+    const Hlle h = hlle(unL, unR, utL, utR, PL, PR, rL, rR, GL, GR, eL, eR, cvL, cvR);
     each_species<NSR>(ns, [&](int s) {
         double L, R;
         state(s, L, R);
-        put(s, fma(L, aL, R * aR));
+        put(s, fma(L, h.aL, R * h.aR));
     });
-    const double mL = rL * aL, mR = rR * aR;
-    put(DIR == 0 ? ns : ns + 1, fma(mL, unL, fma(mR, unR, pP)));
-    put(DIR == 0 ? ns + 1 : ns, fma(mL, utL, mR * utR));
-    put(ns + 2, fma(EL, aL, fma(ER, aR, fma(wL * unL, PL, wR * unR * PR))));
+    put(DIR == 0 ? ns : ns + 1, h.un);
+    put(DIR == 0 ? ns + 1 : ns, h.ut);
+    put(ns + 2, h.E);
 }
 
 // Faces are stored [var][ny][nx + 1] (x) or [var][ny + 1][nx] (y).
-template <int DIR, int NSR>
+template <int DIR>
 __global__ void __launch_bounds__(256) fluid_flux_kernel(WaveTables t, Grid g, const double *Qs, const double *W, double *F)
 {
     const long long f = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -355,59 +415,108 @@ __global__ void __launch_bounds__(256) fluid_flux_kernel(WaveTables t, Grid g, c
     const int fh = DIR == 0 ? g.ny : g.ny + 1;
     const long long fn = (long long)fw * fh;
     if (f >= fn) return;
-    face_flux<DIR, NSR>(t, g, (int)(f % fw), (int)(f / fw), Qs, W, [&](int v, double x) { F[(size_t)v * fn + f] = x; });
+    face_flux<DIR, 0>(t, g, (int)(f % fw), (int)(f / fw), Qs, W, [&](int v, double x) { F[(size_t)v * fn + f] = x; });
 }
 
 // Qout = a0 Q0 + a1 (Q + dt L), L = -(F_{a+1} - F_a) / h (in place allowed: each thread reads
-// and writes only its own cell).  r = dt / h.
-template <int DIR>
-__global__ void fluid_update_kernel(Grid g, const double *Q0, const double *Q, double *Qout, const double *F,
-                                    double r, double a0, double a1)
+// and writes only its own cell).  r = dt / h.  The variables go in groups whose loads are all issued
+// before a store, which the compiler could not move them across; PRIM: then the primitives of the new
+// state for the next stage.
+template <int DIR, bool PRIM>
+__global__ void __launch_bounds__(256) fluid_update_kernel(WaveTables t, Grid g, const double *Q0, const double *Q,
+                                                           double *Qout, const double *F, double r, double a0,
+                                                           double a1, double *W, double *Tc)
 {
     const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= g.n) return;
     const int x = (int)(i % g.nx), y = (int)(i / g.nx);
-    const int nv = g.ns + 3;
     const long long fn = DIR == 0 ? (long long)(g.nx + 1) * g.ny : (long long)g.nx * (g.ny + 1);
     const long long fl = DIR == 0 ? (long long)y * (g.nx + 1) + x : i;
     const long long fr = DIR == 0 ? fl + 1 : fl + g.nx;
-#pragma unroll 4
-    for (int v = 0; v < nv; ++v) {
-        const double q = fma(r, F[(size_t)v * fn + fl] - F[(size_t)v * fn + fr], Q[(size_t)v * g.n + i]);
-        Qout[(size_t)v * g.n + i] = a0 != 0.0 ? a0 * Q0[(size_t)v * g.n + i] + a1 * q : a1 * q;
+    const long long n = g.n;
+    const int nv = g.ns + 3;
+    constexpr int kGroup = 8;
+    for (int v0 = 0; v0 < nv; v0 += kGroup) {
+        double dF[kGroup], q[kGroup], q0[kGroup];
+#pragma unroll
+        for (int k = 0; k < kGroup; ++k) {
+            const size_t v = v0 + k < nv ? v0 + k : nv - 1;
+            dF[k] = F[v * fn + fl] - F[v * fn + fr];
+            q[k] = Q[v * n + i];
+            q0[k] = Q0[v * n + i];
+        }
+#pragma unroll
+        for (int k = 0; k < kGroup; ++k)
+            if (v0 + k < nv) Qout[(size_t)(v0 + k) * n + i] = fma(a0, q0[k], a1 * fma(r, dF[k], q[k]));
     }
+    if constexpr (PRIM) cell_primitives<0>(t, g, 8ull * i, [&](int v) { return Qout[(size_t)v * n + i]; }, W, Tc);
 }
 
-// The update of fluid_update_kernel, then the primitives of the new state for the next stage
-// (the new state stays in registers, so it is not read back).
-template <int DIR, int NSR>
-__global__ void __launch_bounds__(256) fluid_update_prim_kernel(WaveTables t, Grid g, const double *Q0, const double *Q,
-                                                                double *Qout, const double *F, double r, double a0,
-                                                                double a1, double *W, double *Tc)
+// One stage of a sweep in one kernel: the faces of its input, and the update from them in registers, so
+// that no flux goes through memory.  Qout = a0 Q0 + a1 (Q + dt L) as in fluid_update_kernel; PRIM also
+// forms the primitives of Qout.  The input is read at neighbouring cells, so the output is another array,
+// and its primitives go to another set of rows (Wout) than the input's (Win).
+template <int NSR, bool PRIM>
+__device__ __forceinline__ void stage_update(const WaveTables &t, const Grid &g, Off<NSR> o, const double (&Fl)[NSR + 3],
+                                             const double (&Fr)[NSR + 3], const double *Q0, const double *Q, double *Qout,
+                                             double r, double a0, double a1, double *Wout, double *Tc)
 {
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= g.n) return;
-    const int x = (int)(i % g.nx), y = (int)(i / g.nx);
-    const long long fn = DIR == 0 ? (long long)(g.nx + 1) * g.ny : (long long)g.nx * (g.ny + 1);
-    const long long fl = DIR == 0 ? (long long)y * (g.nx + 1) + x : i;
-    const long long fr = DIR == 0 ? fl + 1 : fl + g.nx;
-    auto upd = [&](int v) {
-        const double q = fma(r, F[(size_t)v * fn + fl] - F[(size_t)v * fn + fr], Q[(size_t)v * g.n + i]);
-        const double o = a0 != 0.0 ? a0 * Q0[(size_t)v * g.n + i] + a1 * q : a1 * q;
-        Qout[(size_t)v * g.n + i] = o;
-        return o;
-    };
-    if constexpr (NSR > 0) {
-        double qn[NSR + 3];
+    // (the first stage, a0 = 0, has Q0 = Q: no test stands between the loads)
+    double qn[NSR + 3], q0[NSR + 3];
 #pragma unroll
-        for (int v = 0; v < NSR + 3; ++v) qn[v] = upd(v);
-        cell_primitives<NSR>(t, g, i, [&](int v) { return qn[v]; }, W, Tc);
-    } else {
-        const int nv = g.ns + 3;
-#pragma unroll 4
-        for (int v = 0; v < nv; ++v) upd(v);
-        const long long n = g.n;
-        cell_primitives<0>(t, g, i, [&](int v) { return Qout[(size_t)v * n + i]; }, W, Tc);
+    for (int v = 0; v < NSR + 3; ++v) {
+        qn[v] = ld(Q + (size_t)v * g.n, o);
+        q0[v] = ld(Q0 + (size_t)v * g.n, o);
+    }
+#pragma unroll
+    for (int v = 0; v < NSR + 3; ++v) {
+        qn[v] = fma(a0, q0[v], a1 * fma(r, Fl[v] - Fr[v], qn[v]));
+        st(Qout + (size_t)v * g.n, o, qn[v]);
+    }
+    if constexpr (PRIM) cell_primitives<NSR>(t, g, o, [&](int v) { return qn[v]; }, Wout, Tc);
+}
+
+// Along x a wavefront takes 64 consecutive faces of the rows laid end to end (nx + 1 a row) and updates
+// the cells right of the first 63; a cell's other face comes from the next lane.  No barrier, and one face
+// in 64 is computed twice.
+template <int NSR, bool PRIM>
+__global__ void __launch_bounds__(256) fluid_stage_x_kernel(WaveTables t, Grid g, const double *Q0, const double *Q,
+                                                            double *Qout, const double *Win, double *Wout, double *Tc,
+                                                            double r, double a0, double a1)
+{
+    const int lane = threadIdx.x & 63;
+    const long long f = ((long long)blockIdx.x * 4 + (threadIdx.x >> 6)) * 63 + lane;
+    const int fw = g.nx + 1;
+    const long long nf = (long long)fw * g.ny, fc = f < nf ? f : nf - 1;   // every lane computes a face
+    const int fx = (int)(fc % fw), fy = (int)(fc / fw);
+    double F[NSR + 3], Fr[NSR + 3];
+    face_flux<0, NSR>(t, g, fx, fy, Q, Win, [&](int v, double x) { F[v] = x; });
+#pragma unroll
+    for (int v = 0; v < NSR + 3; ++v) Fr[v] = __shfl_down(F[v], 1);
+    if (lane < 63 && f < nf && fx < g.nx)
+        stage_update<NSR, PRIM>(t, g, 8u * ((unsigned)fy * g.nx + fx), F, Fr, Q0, Q, Qout, r, a0, a1, Wout, Tc);
+}
+
+// Along y a thread walks up `rows` cells of one column, face by face, and keeps the flux of the face
+// below; the first face of a run is the last one of the run underneath, computed by both.
+template <int NSR, bool PRIM>
+__global__ void __launch_bounds__(256) fluid_stage_y_kernel(WaveTables t, Grid g, const double *Q0, const double *Q,
+                                                            double *Qout, const double *Win, double *Wout, double *Tc,
+                                                            double r, double a0, double a1, int rows)
+{
+    const long long k = (long long)blockIdx.x * 256 + threadIdx.x;
+    const int x = (int)(k % g.nx);
+    const long long y0 = k / g.nx * rows;
+    if (y0 >= g.ny) return;
+    const int y1 = (int)(y0 + rows < g.ny ? y0 + rows : g.ny);
+    double F[NSR + 3], Fr[NSR + 3];
+    face_flux<1, NSR>(t, g, x, (int)y0, Q, Win, [&](int v, double q) { F[v] = q; });
+#pragma unroll 1
+    for (int y = (int)y0; y < y1; ++y) {
+        face_flux<1, NSR>(t, g, x, y + 1, Q, Win, [&](int v, double q) { Fr[v] = q; });
+        stage_update<NSR, PRIM>(t, g, 8u * ((unsigned)y * g.nx + x), F, Fr, Q0, Q, Qout, r, a0, a1, Wout, Tc);
+#pragma unroll
+        for (int v = 0; v < NSR + 3; ++v) F[v] = Fr[v];
     }
 }
 
@@ -429,16 +538,16 @@ __global__ void __launch_bounds__(kSpeedThreads) fluid_speed_kernel(WaveTables t
         double rho = 0.0, rR = 0.0, B[6];
         const double T = Tc[i];
         const auto *fl = uniform_table(t.fl);
-        mix_coefs<0>(t, g.ns, T, [&](int s) {
+        mix_coefs<0>(t, g.ns, T, [&](int s) { return Q[(size_t)s * n + i]; }, B);
+        for (int s = 0; s < g.ns; ++s) {
             const double rs = Q[(size_t)s * n + i];
             rho += rs;
             rR = fma(rs, fl[kFluidTab * s + 12], rR);
-            return rs;
-        }, B);
+        }
         const double cv = mix_cv(B, T);
-        const double P = W[(size_t)(g.ns + 2) * n + i];
+        const double P = W[(size_t)2 * n + i];
         const double c = sqrt((cv + rR) / cv * P / rho);
-        double ri = fmax((fabs(W[(size_t)g.ns * n + i]) + c) / dx, (fabs(W[(size_t)(g.ns + 1) * n + i]) + c) / dy);
+        double ri = fmax((fabs(W[i]) + c) / dx, (fabs(W[(size_t)n + i]) + c) / dy);
         if (!(ri >= 0.0)) ri = __builtin_inf();   // a bad cell makes the step size zero
         r = fmax(r, ri);
     }
@@ -474,48 +583,95 @@ __global__ void fluid_energy_back_kernel(Grid g, double *Q, const double *KE, co
     Q[(size_t)(g.ns + 2) * g.n + i] = Es[i] + KE[i];
 }
 
-// f(std::integral_constant<int, NSR>): the species count itself up to kFluidNsRegs, else 0 (streamed)
+// f(std::integral_constant<int, NSR>): the species count itself up to kFluidNsRegs, else (or where 32-bit
+// offsets do not reach) 0, the streamed kernels
 template <int NSR = 1, typename Fn>
-void ns_class(int ns, Fn f)
+void ns_class(const Grid &g, Fn f)
 {
     if constexpr (NSR > kFluidNsRegs) f(std::integral_constant<int, 0>{});
-    else if (ns == NSR) f(std::integral_constant<int, NSR>{});
-    else ns_class<NSR + 1>(ns, f);
+    else if (g.ns == NSR && g.n < (1ll << 29)) f(std::integral_constant<int, NSR>{});
+    else ns_class<NSR + 1>(g, f);
 }
 
 }  // namespace
 
-hipError_t launch_fluid_sweep(const WaveTables &t, const FluidGrid &fg, int dir, double dt, double h,
-                              double *Q, double *Q1, double *W, double *T, double *F, hipStream_t s)
+// Rows that a thread of the y stage walks: its first face is extra work, so as many as leave the device
+// two wavefronts per SIMD (2048), at most kMaxRows
+constexpr int kMaxRows = 8;
+static int rows_per_thread(const Grid &g)
+{
+    const long long r = g.n / (2048 * 64);
+    return r < 1 ? 1 : (r > kMaxRows ? kMaxRows : (int)r);
+}
+
+hipError_t launch_fluid_step(const WaveTables &t, const FluidGrid &fg, double dt, double dx, double dy, bool y_first,
+                             double *Q, double *Q1, double *W, double *T, double *F, hipStream_t s)
 {
     const Grid g{t.ns, fg.nx, fg.ny, fg.bc, (long long)fg.nx * fg.ny};
     const int block = 256;
     const unsigned gc = (unsigned)((g.n + block - 1) / block);
-    const long long nf = dir == 0 ? (long long)(g.nx + 1) * g.ny : (long long)g.nx * (g.ny + 1);
-    const unsigned gf = (unsigned)((nf + block - 1) / block);
-    // (a0, a1, stage input, stage output): Q1 = Q + dt L(Q); Q1 <- 3/4 Q + 1/4 (Q1 + dt L(Q1));
-    // Q <- 1/3 Q + 2/3 (Q1 + dt L(Q1))
+    // (a0, a1, stage input, stage output): Q1 = Q + dt L(Q); Q2 = 3/4 Q + 1/4 (Q1 + dt L(Q1));
+    // Q <- 1/3 Q + 2/3 (Q2 + dt L(Q2))
     const double a0[3] = {0.0, 0.75, 1.0 / 3.0}, a1[3] = {1.0, 0.25, 2.0 / 3.0};
-    // stage k: faces of its input's primitives, then the update, which in stages 0 and 1 also
-    // forms the primitives of its output for the next stage
-    ns_class(g.ns, [&](auto nsrc) {
+    ns_class(g, [&](auto nsrc) {
         constexpr int NSR = decltype(nsrc)::value;
-        hipLaunchKernelGGL((fluid_prim_kernel<NSR>), dim3(gc), dim3(block), 0, s, t, g, Q, W, T);
-        auto stage = [&](auto dirc, const double *in, double *out, int k) {
-            constexpr int D = decltype(dirc)::value;
-            hipLaunchKernelGGL((fluid_flux_kernel<D, NSR>), dim3(gf), dim3(block), 0, s, t, g, in, W, F);
-            if (k == 2)
-                hipLaunchKernelGGL(fluid_update_kernel<D>, dim3(gc), dim3(block), 0, s, g, Q, in, out, F, dt / h, a0[k],
-                                   a1[k]);
-            else
-                hipLaunchKernelGGL((fluid_update_prim_kernel<D, NSR>), dim3(gc), dim3(block), 0, s, t, g, Q, in, out, F,
-                                   dt / h, a0[k], a1[k], W, T);
-        };
-        for (int k = 0; k < 3; ++k) {
-            const double *in = k == 0 ? Q : Q1;
-            double *out = k == 2 ? Q : Q1;
-            if (dir == 0) stage(std::integral_constant<int, 0>{}, in, out, k);
-            else stage(std::integral_constant<int, 1>{}, in, out, k);
+        if constexpr (NSR > 0) {
+            // Q2 takes the place of the fluxes; the primitives alternate between two sets of rows
+            double *const buf[3] = {Q, Q1, F}, *const prim[2] = {W, W + (size_t)3 * g.n};
+            hipLaunchKernelGGL((fluid_prim_kernel<NSR>), dim3(gc), dim3(block), 0, s, t, g, Q, prim[0], T);
+            int w = 0;
+            for (int sweep = 0; sweep < 2; ++sweep) {
+                const bool along_x = (sweep == 0) != y_first;
+                const double r = dt / (along_x ? dx : dy);
+                for (int k = 0; k < 3; ++k, w ^= 1) {
+                    const double *in = buf[k];
+                    double *out = buf[(k + 1) % 3];
+                    const bool last = sweep == 1 && k == 2;   // no stage reads its primitives
+                    if (along_x) {
+                        const long long waves = ((long long)(g.nx + 1) * g.ny + 62) / 63;
+                        const unsigned gx = (unsigned)((waves + 3) / 4);
+                        if (last)
+                            hipLaunchKernelGGL((fluid_stage_x_kernel<NSR, false>), dim3(gx), dim3(block), 0, s, t, g, Q, in, out,
+                                               prim[w], prim[w ^ 1], T, r, a0[k], a1[k]);
+                        else
+                            hipLaunchKernelGGL((fluid_stage_x_kernel<NSR, true>), dim3(gx), dim3(block), 0, s, t, g, Q, in, out,
+                                               prim[w], prim[w ^ 1], T, r, a0[k], a1[k]);
+                    } else {
+                        const int rows = rows_per_thread(g);
+                        const long long threads = (long long)g.nx * ((g.ny + rows - 1) / rows);
+                        const unsigned gy = (unsigned)((threads + block - 1) / block);
+                        if (last)
+                            hipLaunchKernelGGL((fluid_stage_y_kernel<NSR, false>), dim3(gy), dim3(block), 0, s, t, g, Q, in, out,
+                                               prim[w], prim[w ^ 1], T, r, a0[k], a1[k], rows);
+                        else
+                            hipLaunchKernelGGL((fluid_stage_y_kernel<NSR, true>), dim3(gy), dim3(block), 0, s, t, g, Q, in, out,
+                                               prim[w], prim[w ^ 1], T, r, a0[k], a1[k], rows);
+                    }
+                }
+            }
+        } else {
+            // larger mixtures: a stage is its faces' kernel, then the update's, which in the first two
+            // stages also forms the primitives of its output
+            auto sweep = [&](auto dirc) {
+                constexpr int D = decltype(dirc)::value;
+                const long long nf = D == 0 ? (long long)(g.nx + 1) * g.ny : (long long)g.nx * (g.ny + 1);
+                const unsigned gf = (unsigned)((nf + block - 1) / block);
+                const double r = dt / (D == 0 ? dx : dy);
+                hipLaunchKernelGGL((fluid_prim_kernel<0>), dim3(gc), dim3(block), 0, s, t, g, Q, W, T);
+                for (int k = 0; k < 3; ++k) {
+                    const double *in = k == 0 ? Q : Q1;
+                    hipLaunchKernelGGL((fluid_flux_kernel<D>), dim3(gf), dim3(block), 0, s, t, g, in, W, F);
+                    if (k == 2)
+                        hipLaunchKernelGGL((fluid_update_kernel<D, false>), dim3(gc), dim3(block), 0, s, t, g, Q, in, Q, F, r,
+                                           a0[k], a1[k], W, T);
+                    else
+                        hipLaunchKernelGGL((fluid_update_kernel<D, true>), dim3(gc), dim3(block), 0, s, t, g, Q, in, Q1, F, r,
+                                           a0[k], a1[k], W, T);
+                }
+            };
+            if (y_first) sweep(std::integral_constant<int, 1>{});
+            sweep(std::integral_constant<int, 0>{});
+            if (!y_first) sweep(std::integral_constant<int, 1>{});
         }
     });
     return hipGetLastError();
@@ -527,7 +683,7 @@ hipError_t launch_fluid_speed(const WaveTables &t, const FluidGrid &fg, const do
     const Grid g{t.ns, fg.nx, fg.ny, fg.bc, (long long)fg.nx * fg.ny};
     const int block = 256;
     const unsigned gc = (unsigned)((g.n + block - 1) / block);
-    ns_class(g.ns, [&](auto nsrc) {
+    ns_class(g, [&](auto nsrc) {
         constexpr int NSR = decltype(nsrc)::value;
         hipLaunchKernelGGL((fluid_prim_kernel<NSR>), dim3(gc), dim3(block), 0, s, t, g, Q, W, T);
     });

@@ -226,11 +226,12 @@ hipError_t scratch_address(int device, unsigned char **out);
 struct FluidGrid {
     int nx, ny, bc;
 };
-// One dimensionally split sweep (dir 0 = x, 1 = y) of dt: three Runge-Kutta stages of the MP5 /
-// HLLE update, Q in place; Q1 (stage state), W (primitives), T (temperatures, also the Newton
-// start values) and F (face fluxes, (ns + 3) (nx + 1) (ny + 1) doubles) are workspace.
-hipError_t launch_fluid_sweep(const WaveTables &t, const FluidGrid &g, int dir, double dt, double h, double *Q,
-                              double *Q1, double *W, double *T, double *F, hipStream_t s);
+// One dimensionally split step of dt, an x sweep then a y sweep (the reverse with y_first), each three
+// Runge-Kutta stages of the MP5 / HLLE update, Q in place; Q1 (stage state), W (primitives, 6 n doubles),
+// T (temperatures, also the Newton start values) and F (a second stage state, or the face fluxes,
+// (ns + 3) (nx + 1) (ny + 1) doubles) are workspace.
+hipError_t launch_fluid_step(const WaveTables &t, const FluidGrid &g, double dt, double dx, double dy, bool y_first,
+                             double *Q, double *Q1, double *W, double *T, double *F, hipStream_t s);
 // Largest (|u| + c) / dx, (|v| + c) / dy over the grid into *out (bit pattern, zero beforehand).
 hipError_t launch_fluid_speed(const WaveTables &t, const FluidGrid &g, const double *Q, double *W, double *T,
                               double dx, double dy, unsigned long long *out, hipStream_t s);

@@ -1628,12 +1628,12 @@ kin_status kin_fluid_create(kin_ctx *ctx, int32_t mech_id, int32_t nx, int32_t n
     const size_t n = (size_t)nx * ny, nv = (size_t)m.h.ns + 3;
     const size_t nf = nv * (size_t)(nx + 1) * (ny + 1);
     auto up = [](size_t d) { return (d + 31) & ~(size_t)31; };
-    const size_t doubles = 3 * up(nv * n) + 3 * up(n) + 32 + up(nf);
+    const size_t doubles = 2 * up(nv * n) + up(6 * n) + 3 * up(n) + 32 + up(nf);
     KIN_HIP(ctx, hipMalloc(&f->buf, sizeof(double) * doubles));
     double *p = static_cast<double *>(f->buf);
     f->Q = p; p += up(nv * n);
     f->Q1 = p; p += up(nv * n);
-    f->W = p; p += up(nv * n);
+    f->W = p; p += up(6 * n);   // two sets of u, v, P
     f->T = p; p += up(n);
     f->KE = p; p += up(n);
     f->Es = p; p += up(n);
@@ -1723,10 +1723,7 @@ kin_status kin_fluid_max_dt(kin_ctx *ctx, int32_t fluid_id, double cfl, double *
 
 static kin_status fluid_step(kin_ctx *ctx, Fluid &f, Mech &m, double dt, int y_first, hipStream_t st)
 {
-    for (int k = 0; k < 2; ++k) {
-        const int dir = (k == 0) == (y_first == 0) ? 0 : 1;
-        KIN_HIP(ctx, launch_fluid_sweep(m.tab, f.g, dir, dt, dir == 0 ? f.dx : f.dy, f.Q, f.Q1, f.W, f.T, f.F, st));
-    }
+    KIN_HIP(ctx, launch_fluid_step(m.tab, f.g, dt, f.dx, f.dy, y_first != 0, f.Q, f.Q1, f.W, f.T, f.F, st));
     return KIN_OK;
 }
 

@@ -56,6 +56,27 @@ def test_fluid_steps_two_ranges(ns, bc, T):
         assert np.all(d <= 1e-10), d
 
 
+@pytest.mark.parametrize("nx,ny,bc", [(1, 1, 1), (1, 70, 1), (62, 3, 0), (63, 5, 1), (64, 4, 0), (125, 3, 1), (127, 3, 0),
+                                      (641, 410, 1), (1030, 1031, 0)])
+def test_fluid_step_tiles(nx, ny, bc):
+    """Row lengths around the 63 cells of a wavefront, fewer cells than a wavefront has, and columns that a
+    thread walks over several rows with a ragged last run."""
+    from oracle import fluid_oracle as fo
+    from paper_1110_4903_amd import kin
+    m = two_range(4, 7)
+    gas = fo.Gas(m)
+    dx, dy = 1e-3 / nx, 1e-3 / ny
+    Q = np.ascontiguousarray(flow_state(fo, gas, nx, ny, 3, 500.0, 1800.0))
+    with kin.Context(0) as ctx:
+        fid = ctx.fluid_create(ctx.mech_upload(m), nx, ny, dx, dy, bc)
+        ctx.fluid_upload(fid, Q)
+        dt = fo.max_dt(gas, Q, dx, dy, 0.4)
+        ctx.fluid_step(fid, dt, y_first=bool(nx % 2))
+        d = scaled_diff(ctx.fluid_download(fid), fo.fluid_step(gas, Q, dt, dx, dy, "outflow" if bc else "periodic",
+                                                               y_first=bool(nx % 2)))
+        assert np.all(d <= 1e-10), d
+
+
 def test_fluid_invalid_cell_stays_visible():
     """A cell that is not a number makes the step size zero, and spreads to its neighbours' states
     instead of being clipped away by the limiter."""
