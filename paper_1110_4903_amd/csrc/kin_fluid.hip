@@ -13,24 +13,27 @@
 //                flux between them (Eq. fluxhlle);
 //   update       per cell: the stage's combination of the sweep's start state, the stage state
 //                and dt times the flux difference.
-// Up to 16 species one kernel does a stage: a cell's two fluxes, its update and the primitives of
-// its new state stay in registers (fluid_stage_x_kernel, fluid_stage_y_kernel), and only the step's
-// first primitives have a kernel of their own.  Larger mixtures do a stage in two kernels, with the
-// fluxes in memory.  One thread per cell or face; consecutive threads take consecutive x, so every
-// array access of a wavefront is one or two contiguous runs of a row.  The six-cell stencil is read
-// from the state and primitive arrays, which neighbouring threads share through the caches.
+// One kernel does a stage: a cell's two fluxes, its update and the primitives of its new state stay
+// in registers, and only the step's first primitives have a kernel of their own.  Up to 16 species a
+// lane does all of a face and a cell (fluid_stage_kernel), up to 64 four wavefronts share them
+// (fluid_wide_kernel).  Larger mixtures, and grids whose arrays exceed 32-bit offsets, do a stage in
+// two kernels, with the fluxes in memory.  Consecutive lanes take consecutive x, so an access of a
+// wavefront is a few contiguous runs of a row.  The six-cell stencil is read from the state and
+// primitive arrays, which neighbouring lanes share through the caches.
 //
-// What bounds it: a fused stage of nine species on 1024 x 1024 cells takes 113 us along x and 143 us
-// along y, where its 352 bytes a cell at the rate of a large copy (4.7 TB/s) would take 79 us; two
-// wavefronts per SIMD (about 210 and 240 registers: the six-cell loads of nine species in flight)
-// hide the rest of the latency incompletely, and a bound on the registers makes the compiler spill
-// (2.8 ms a step with three wavefronts).  A step takes 1.58 ms; 1.93 ms with the fluxes in memory (a
-// stage's faces 58-82 us, its update with primitives 73-100 us), 2.33 ms when also each limiter had a
-// division and branches, every coefficient was selected per lane and the energies were summed species
-// by species.  3750 cells: 135 us, 182 us and 323 us, of which the fused form saves launches and the
-// update its test on a0 per variable, which put each variable's loads behind the last one's.
-// 100250 cells of 36 species: 0.93 ms, from 2.22 ms whose Newton summed over the species in every
-// iteration.
+// What bounds it: a stage of nine species on 1024 x 1024 cells takes 107 us along x and 127 us along
+// y, where its 352 bytes a cell at the rate of a large copy (4.7 TB/s) would take 79 us; two
+// wavefronts per SIMD (208 registers: the six-cell loads of nine species in flight) hide the rest of
+// the latency incompletely, and a bound on the registers makes the compiler spill (three wavefronts:
+// 1.8 times the time).  36 species on 401 x 250 cells: 36 and 42 us, of 34 us of traffic that the
+// caches partly hold.  3750 cells of nine species: 8-9 us a stage, the latency of one wavefront.
+// us a step, 1024 x 1024 of 9 / 75 x 50 of 9 / 401 x 250 of 36 species:
+//   1166 / 162 / 1111  a division and branches in each limiter, a selection of every coefficient per
+//                      lane, energies summed species by species
+//    963 /  91 /  493  without those; three kernels a stage (faces 58-82 us, update with primitives
+//                      73-100 us on the large grid)
+//    777 /  67 /  468  one kernel a stage up to 16 species, along y a walk up the columns
+//    687 /  57 /  247  tiles along y, tiles to XCDs in contiguous parts, the wide form
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -476,48 +479,277 @@ __device__ __forceinline__ void stage_update(const WaveTables &t, const Grid &g,
     if constexpr (PRIM) cell_primitives<NSR>(t, g, o, [&](int v) { return qn[v]; }, Wout, Tc);
 }
 
-// Along x a wavefront takes 64 consecutive faces of the rows laid end to end (nx + 1 a row) and updates
-// the cells right of the first 63; a cell's other face comes from the next lane.  No barrier, and one face
-// in 64 is computed twice.
-template <int NSR, bool PRIM>
-__global__ void __launch_bounds__(256) fluid_stage_x_kernel(WaveTables t, Grid g, const double *Q0, const double *Q,
-                                                            double *Qout, const double *Win, double *Wout, double *Tc,
-                                                            double r, double a0, double a1)
+// Faces of a wavefront.  Along x 64 consecutive ones of the rows laid end to end (nx + 1 a row), and the
+// cells right of the first 63.  Along y a tile of 2^lw columns by 64 / 2^lw faces and the cells above all
+// but the last of each column.  A cell's other face comes from the lane `next` further on: no barrier, and
+// one face of a run is computed twice.
+struct Tile {
+    int fx, fy;     // the lane's face
+    int next;
+    bool active;    // the lane has a cell
+};
+// Consecutive blocks go to the eight XCDs in turn, each with an L2 of its own: block b of the grid (a
+// multiple of eight) takes a place in one of eight contiguous parts, so that the rows and cache lines that
+// neighbouring tiles share are read into one L2.
+__device__ __forceinline__ unsigned xcd_block()
 {
-    const int lane = threadIdx.x & 63;
-    const long long f = ((long long)blockIdx.x * 4 + (threadIdx.x >> 6)) * 63 + lane;
-    const int fw = g.nx + 1;
-    const long long nf = (long long)fw * g.ny, fc = f < nf ? f : nf - 1;   // every lane computes a face
-    const int fx = (int)(fc % fw), fy = (int)(fc / fw);
-    double F[NSR + 3], Fr[NSR + 3];
-    face_flux<0, NSR>(t, g, fx, fy, Q, Win, [&](int v, double x) { F[v] = x; });
-#pragma unroll
-    for (int v = 0; v < NSR + 3; ++v) Fr[v] = __shfl_down(F[v], 1);
-    if (lane < 63 && f < nf && fx < g.nx)
-        stage_update<NSR, PRIM>(t, g, 8u * ((unsigned)fy * g.nx + fx), F, Fr, Q0, Q, Qout, r, a0, a1, Wout, Tc);
+    return (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
 }
 
-// Along y a thread walks up `rows` cells of one column, face by face, and keeps the flux of the face
-// below; the first face of a run is the last one of the run underneath, computed by both.
-template <int NSR, bool PRIM>
-__global__ void __launch_bounds__(256) fluid_stage_y_kernel(WaveTables t, Grid g, const double *Q0, const double *Q,
-                                                            double *Qout, const double *Win, double *Wout, double *Tc,
-                                                            double r, double a0, double a1, int rows)
+template <int DIR>
+__device__ __forceinline__ Tile stage_tile(const Grid &g, long long wave, int lane, int lw)
 {
-    const long long k = (long long)blockIdx.x * 256 + threadIdx.x;
-    const int x = (int)(k % g.nx);
-    const long long y0 = k / g.nx * rows;
-    if (y0 >= g.ny) return;
-    const int y1 = (int)(y0 + rows < g.ny ? y0 + rows : g.ny);
-    double F[NSR + 3], Fr[NSR + 3];
-    face_flux<1, NSR>(t, g, x, (int)y0, Q, Win, [&](int v, double q) { F[v] = q; });
-#pragma unroll 1
-    for (int y = (int)y0; y < y1; ++y) {
-        face_flux<1, NSR>(t, g, x, y + 1, Q, Win, [&](int v, double q) { Fr[v] = q; });
-        stage_update<NSR, PRIM>(t, g, 8u * ((unsigned)y * g.nx + x), F, Fr, Q0, Q, Qout, r, a0, a1, Wout, Tc);
-#pragma unroll
-        for (int v = 0; v < NSR + 3; ++v) F[v] = Fr[v];
+    if constexpr (DIR == 0) {
+        const long long f = wave * 63 + lane;
+        const int fw = g.nx + 1;
+        const long long nf = (long long)fw * g.ny, fc = f < nf ? f : nf - 1;   // every lane computes a face
+        const int fx = (int)(fc % fw);
+        return {fx, (int)(fc / fw), 1, lane < 63 && f < nf && fx < g.nx};
+    } else {
+        const int width = 1 << lw, height = 64 >> lw, tiles = (g.nx + width - 1) >> lw;
+        const int x = (int)(wave % tiles) * width + (lane & (width - 1));
+        const long long y = wave / tiles * (height - 1) + (lane >> lw);
+        return {x < g.nx ? x : g.nx - 1, (int)(y < g.ny ? y : g.ny), width, (lane >> lw) < height - 1 && x < g.nx && y < g.ny};
     }
+}
+
+template <int DIR, int NSR, bool PRIM>
+__global__ void __launch_bounds__(256) fluid_stage_kernel(WaveTables t, Grid g, const double *Q0, const double *Q,
+                                                          double *Qout, const double *Win, double *Wout, double *Tc,
+                                                          double r, double a0, double a1, int lw)
+{
+    const int lane = threadIdx.x & 63;
+    const Tile c = stage_tile<DIR>(g, (long long)xcd_block() * 4 + (threadIdx.x >> 6), lane, lw);
+    double F[NSR + 3], Fr[NSR + 3];
+    face_flux<DIR, NSR>(t, g, c.fx, c.fy, Q, Win, [&](int v, double x) { F[v] = x; });
+#pragma unroll
+    for (int v = 0; v < NSR + 3; ++v) Fr[v] = __shfl_down(F[v], c.next);
+    if (c.active)
+        stage_update<NSR, PRIM>(t, g, 8u * ((unsigned)c.fy * g.nx + c.fx), F, Fr, Q0, Q, Qout, r, a0, a1, Wout, Tc);
+}
+
+// ---- A stage of larger mixtures: kWide wavefronts work on the same 64 faces (or cells), lane by lane,
+// each on its own run of at most NSG species, whose face states stay in its registers; sums over the
+// species go through LDS, and every wavefront then evaluates the face's (cell's) scalars for itself.
+constexpr int kWide = 4;
+
+// LDS of a block, [..][64 lanes].  The arrays of one union alternate: between two writes of it, and
+// between a write and the last reads of the other member, lies a barrier of the other union's exchange.
+struct WideShared {
+    union {
+        struct {
+            double sum[kWide][4][64];    // face: rho and rho R of the left and the right state
+            double prim[3][2][64];       // the states of u, v, P
+        } f;
+        struct {
+            double sum[kWide][2][64];    // cell: rho and rho R
+            double var[3][64];           // momenta and energy
+        } c;
+    } a;
+    union {
+        double e[kWide][4][64];          // face: energy and heat capacity of both states
+        double B[kWide][6][64];          // cell: coefficients of the mixture's energy
+    } b;
+};
+
+// A wavefront's species are s0 .. s0 + NSG - 1; those from ns on are the last species with no density.
+template <int NSG> struct WideRun {
+    int w, s0, ns;
+    __device__ __forceinline__ int row(int j) const { return s0 + j < ns ? s0 + j : ns - 1; }
+    __device__ __forceinline__ bool has(int j) const { return s0 + j < ns; }
+    // the variable that the wavefront has besides: a momentum or the energy (none in the others)
+    __device__ __forceinline__ int extra() const { return w < 3 ? w : 2; }
+};
+
+// Fluxes of the wavefront's species into F[0..NSG-1], of its momentum or energy into F[NSG].
+template <int DIR, int NSG>
+__device__ __forceinline__ void face_flux_wide(const WaveTables &t, const Grid &g, const WideRun<NSG> &run, int lane, int fx,
+                                               int fy, const double *Qs, const double *W, WideShared &sh,
+                                               double (&F)[NSG + 1])
+{
+    const int a = DIR == 0 ? fx : fy;
+    const int len = DIR == 0 ? g.nx : g.ny;
+    const long long n = g.n;
+    unsigned c[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        const int q = wrap(a - 3 + k, len, g.bc);
+        c[k] = 8 * (DIR == 0 ? (unsigned)fy * g.nx + q : (unsigned)q * g.nx + fx);
+    }
+    auto recon = [&](const double *w, double &L, double &R) {
+        const double v0 = ld(w, c[0]), v1 = ld(w, c[1]), v2 = ld(w, c[2]), v3 = ld(w, c[3]), v4 = ld(w, c[4]), v5 = ld(w, c[5]);
+        L = mp5(v0, v1, v2, v3, v4);
+        R = mp5(v5, v4, v3, v2, v1);
+    };
+    double Ls[NSG], Rv[NSG], pl, pr;
+    recon(W + (size_t)run.extra() * n, pl, pr);
+#pragma unroll
+    for (int j = 0; j < NSG; ++j) {
+        recon(Qs + (size_t)run.row(j) * n, Ls[j], Rv[j]);
+        if (!run.has(j)) Ls[j] = Rv[j] = 0.0;
+    }
+    const auto *fl = uniform_table(t.fl);
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+#pragma unroll
+    for (int j = 0; j < NSG; ++j) {
+        const double Rs = fl[kFluidTab * run.row(j) + 12];
+        s0 += Ls[j];
+        s1 += Rv[j];
+        s2 = fma(Ls[j], Rs, s2);
+        s3 = fma(Rv[j], Rs, s3);
+    }
+    auto &A = sh.a.f;
+    A.sum[run.w][0][lane] = s0;
+    A.sum[run.w][1][lane] = s1;
+    A.sum[run.w][2][lane] = s2;
+    A.sum[run.w][3][lane] = s3;
+    if (run.w < 3) {
+        A.prim[run.w][0][lane] = pl;
+        A.prim[run.w][1][lane] = pr;
+    }
+    __syncthreads();
+    double rL = 0.0, rR = 0.0, GL = 0.0, GR = 0.0;
+#pragma unroll
+    for (int k = 0; k < kWide; ++k) {
+        rL += A.sum[k][0][lane];
+        rR += A.sum[k][1][lane];
+        GL += A.sum[k][2][lane];
+        GR += A.sum[k][3][lane];
+    }
+    const double unL = A.prim[DIR == 0 ? 0 : 1][0][lane], unR = A.prim[DIR == 0 ? 0 : 1][1][lane];
+    const double utL = A.prim[DIR == 0 ? 1 : 0][0][lane], utR = A.prim[DIR == 0 ? 1 : 0][1][lane];
+    const double PL = A.prim[2][0][lane], PR = A.prim[2][1][lane];
+    const double TL = PL * recip(GL), TR = PR * recip(GR);
+    auto row = [&](int j) { return run.row(j); };
+    double B[6];
+    mix_coefs<NSG>(t, NSG, TL, [&](int j) { return Ls[j]; }, row, B);
+    sh.b.e[run.w][0][lane] = mix_energy(B, TL);
+    sh.b.e[run.w][1][lane] = mix_cv(B, TL);
+    mix_coefs<NSG>(t, NSG, TR, [&](int j) { return Rv[j]; }, row, B);
+    sh.b.e[run.w][2][lane] = mix_energy(B, TR);
+    sh.b.e[run.w][3][lane] = mix_cv(B, TR);
+    __syncthreads();
+    double eL = 0.0, cvL = 0.0, eR = 0.0, cvR = 0.0;
+#pragma unroll
+    for (int k = 0; k < kWide; ++k) {
+        eL += sh.b.e[k][0][lane];
+        cvL += sh.b.e[k][1][lane];
+        eR += sh.b.e[k][2][lane];
+        cvR += sh.b.e[k][3][lane];
+    }
+    const Hlle h = hlle(unL, unR, utL, utR, PL, PR, rL, rR, GL, GR, eL, eR, cvL, cvR);
+#pragma unroll
+    for (int j = 0; j < NSG; ++j) F[j] = fma(Ls[j], h.aL, Rv[j] * h.aR);
+    F[NSG] = run.w == (DIR == 0 ? 0 : 1) ? h.un : (run.w == (DIR == 0 ? 1 : 0) ? h.ut : h.E);
+}
+
+// stage_update for the wavefront's variables of a cell (active: of the grid, and this lane's), then, with
+// PRIM, its primitives: every wavefront iterates on the same sums, one stores T, u, v and P each.
+template <int NSG, bool PRIM>
+__device__ __forceinline__ void stage_update_wide(const WaveTables &t, const Grid &g, const WideRun<NSG> &run, int lane,
+                                                  bool active, unsigned o, const double (&Fl)[NSG + 1],
+                                                  const double (&Fr)[NSG + 1], const double *Q0, const double *Q,
+                                                  double *Qout, double r, double a0, double a1, double *W, double *Tc,
+                                                  WideShared &sh)
+{
+    const long long n = g.n;
+    double qn[NSG + 1], q0[NSG + 1];
+#pragma unroll
+    for (int j = 0; j < NSG + 1; ++j) {
+        const size_t v = j < NSG ? run.row(j) : run.ns + run.extra();
+        qn[j] = ld(Q + v * n, o);
+        q0[j] = ld(Q0 + v * n, o);
+    }
+    double T = 0.0;
+    if constexpr (PRIM) T = ld(Tc, o);
+#pragma unroll
+    for (int j = 0; j < NSG + 1; ++j) {
+        qn[j] = fma(a0, q0[j], a1 * fma(r, Fl[j] - Fr[j], qn[j]));
+        const bool mine = j < NSG ? run.has(j) : run.w < 3;
+        const size_t v = j < NSG ? run.row(j) : run.ns + run.extra();
+        if (mine && active) st(Qout + v * n, o, qn[j]);
+        if (j < NSG && !mine) qn[j] = 0.0;
+    }
+    if constexpr (PRIM) {
+        const auto *fl = uniform_table(t.fl);
+        double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+        for (int j = 0; j < NSG; ++j) {
+            s0 += qn[j];
+            s1 = fma(qn[j], fl[kFluidTab * run.row(j) + 12], s1);
+        }
+        auto &C = sh.a.c;
+        C.sum[run.w][0][lane] = s0;
+        C.sum[run.w][1][lane] = s1;
+        if (run.w < 3) C.var[run.w][lane] = qn[NSG];
+        __syncthreads();
+        double rho = 0.0, rR = 0.0;
+#pragma unroll
+        for (int k = 0; k < kWide; ++k) {
+            rho += C.sum[k][0][lane];
+            rR += C.sum[k][1][lane];
+        }
+        const double ir = 1.0 / rho;
+        const double u = C.var[0][lane] * ir, v = C.var[1][lane] * ir;
+        const double eint = C.var[2][lane] - 0.5 * rho * (u * u + v * v);
+        if (!(T >= 100.0 && T <= 1e4)) T = 1000.0;
+        // the iteration of cell_primitives; the block sums coefficients again while a lane has left the
+        // interval that its own hold for (the vote is over the block, so all wavefronts do the same)
+        bool go = active;
+        int it = 0;
+        for (int sums = 0; sums < 60; ++sums) {
+            double B[6], lo, hi;
+            mix_coefs<NSG>(t, NSG, T, [&](int j) { return qn[j]; }, [&](int j) { return run.row(j); }, B);
+#pragma unroll
+            for (int k = 0; k < 6; ++k) sh.b.B[run.w][k][lane] = B[k];
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < 6; ++k) {
+                B[k] = 0.0;
+#pragma unroll
+                for (int q = 0; q < kWide; ++q) B[k] += sh.b.B[q][k][lane];
+            }
+            range_interval<0>(t, run.ns, T, lo, hi);
+            while (go && it < 60 && T >= lo && T < hi) {
+                const double dT = (mix_energy(B, T) - eint) * recip(mix_cv(B, T));
+                T -= dT;
+                go = fabs(dT) > 1e-13 * fabs(T);
+                ++it;
+            }
+            if (!__syncthreads_or(go && it < 60 && T == T)) break;
+        }
+        if (active) {
+            if (run.w == 0) st(Tc, o, T);
+            if (run.w == 1) st(W, o, u);
+            if (run.w == 2) st(W + n, o, v);
+            if (run.w == 3) st(W + 2 * n, o, rR * T);
+        }
+    }
+}
+
+template <int NSG> __device__ __forceinline__ WideRun<NSG> wide_run(const Grid &g)
+{
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    return {w, w * NSG, g.ns};
+}
+
+// fluid_stage_kernel with a block per 64 faces.
+template <int DIR, int NSG, bool PRIM>
+__global__ void __launch_bounds__(64 * kWide) fluid_wide_kernel(WaveTables t, Grid g, const double *Q0, const double *Q,
+                                                                double *Qout, const double *Win, double *Wout, double *Tc,
+                                                                double r, double a0, double a1, int lw)
+{
+    __shared__ WideShared sh;
+    const WideRun<NSG> run = wide_run<NSG>(g);
+    const int lane = threadIdx.x & 63;
+    const Tile c = stage_tile<DIR>(g, xcd_block(), lane, lw);
+    double F[NSG + 1], Fr[NSG + 1];
+    face_flux_wide<DIR, NSG>(t, g, run, lane, c.fx, c.fy, Q, Win, sh, F);
+#pragma unroll
+    for (int j = 0; j < NSG + 1; ++j) Fr[j] = __shfl_down(F[j], c.next);
+    const int x = c.fx < g.nx ? c.fx : g.nx - 1, y = c.fy < g.ny ? c.fy : g.ny - 1;
+    stage_update_wide<NSG, PRIM>(t, g, run, lane, c.active, 8u * ((unsigned)y * g.nx + x), F, Fr, Q0, Q, Qout, r, a0, a1, Wout,
+                                 Tc, sh);
 }
 
 // Largest (|u| + c) / dx and (|v| + c) / dy over the grid (positive doubles order like their
@@ -583,26 +815,53 @@ __global__ void fluid_energy_back_kernel(Grid g, double *Q, const double *KE, co
     Q[(size_t)(g.ns + 2) * g.n + i] = Es[i] + KE[i];
 }
 
-// f(std::integral_constant<int, NSR>): the species count itself up to kFluidNsRegs, else (or where 32-bit
-// offsets do not reach) 0, the streamed kernels
-template <int NSR = 1, typename Fn>
+// f(N, Wide): up to kFluidNsRegs species the kernels compiled for N of them; up to kWide times as many
+// those of a block's wavefronts that take N each; else (or where 32-bit offsets do not reach) N = 0, the
+// streamed kernels
+template <int N = 1, typename Fn>
 void ns_class(const Grid &g, Fn f)
 {
-    if constexpr (NSR > kFluidNsRegs) f(std::integral_constant<int, 0>{});
-    else if (g.ns == NSR && g.n < (1ll << 29)) f(std::integral_constant<int, NSR>{});
-    else ns_class<NSR + 1>(g, f);
+    if constexpr (N > kFluidNsRegs) {
+        f(std::integral_constant<int, 0>{}, std::false_type{});
+    } else {
+        const bool small = g.n < (1ll << 29);
+        if (small && g.ns == N) f(std::integral_constant<int, N>{}, std::false_type{});
+        else if (N * kWide > kFluidNsRegs && small && g.ns > kFluidNsRegs && (g.ns + kWide - 1) / kWide == N) {
+            if constexpr (N * kWide > kFluidNsRegs) f(std::integral_constant<int, N>{}, std::true_type{});
+        } else ns_class<N + 1>(g, f);
+    }
+}
+
+// Width (its logarithm) of a tile of the stages along y, of a grid that is that wide: 8 columns by 8 faces
+// compute 8/7 of the faces and read 64 contiguous bytes at a time.  Nine species on 1024 x 1024 cells,
+// 36 on 401 x 250, us a step: width 4 774 and 385, 8 687 and 247, 16 693 and 255 (4 without the
+// assignment of tiles to XCDs).  A thread that walks 8 rows of a column instead, 777 and 388.
+constexpr int kTileLog = 3;
+
+// One stage, its input's primitives in Win and its output's to Wout (PRIM).
+template <int N, bool WIDE, bool PRIM>
+void launch_stage(const WaveTables &t, const Grid &g, bool along_x, const double *Q0, const double *Q, double *Qout,
+                  const double *Win, double *Wout, double *T, double r, double a0, double a1, hipStream_t s)
+{
+    int lw = 0;
+    while (lw < kTileLog && (1 << lw) < g.nx) ++lw;
+    const int height = 64 >> lw;
+    const long long waves = along_x ? ((long long)(g.nx + 1) * g.ny + 62) / 63
+                                    : (long long)((g.nx + (1 << lw) - 1) >> lw) * ((g.ny + height - 2) / (height - 1));
+    const dim3 block(WIDE ? 64 * kWide : 256), grid((unsigned)(((WIDE ? waves : (waves + 3) / 4) + 7) / 8 * 8));
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, s, t, g, Q0, Q, Qout, Win, Wout, T, r, a0, a1, lw);
+    };
+    if constexpr (WIDE) {
+        if (along_x) go(fluid_wide_kernel<0, N, PRIM>);
+        else go(fluid_wide_kernel<1, N, PRIM>);
+    } else {
+        if (along_x) go(fluid_stage_kernel<0, N, PRIM>);
+        else go(fluid_stage_kernel<1, N, PRIM>);
+    }
 }
 
 }  // namespace
-
-// Rows that a thread of the y stage walks: its first face is extra work, so as many as leave the device
-// two wavefronts per SIMD (2048), at most kMaxRows
-constexpr int kMaxRows = 8;
-static int rows_per_thread(const Grid &g)
-{
-    const long long r = g.n / (2048 * 64);
-    return r < 1 ? 1 : (r > kMaxRows ? kMaxRows : (int)r);
-}
 
 hipError_t launch_fluid_step(const WaveTables &t, const FluidGrid &fg, double dt, double dx, double dy, bool y_first,
                              double *Q, double *Q1, double *W, double *T, double *F, hipStream_t s)
@@ -613,65 +872,46 @@ hipError_t launch_fluid_step(const WaveTables &t, const FluidGrid &fg, double dt
     // (a0, a1, stage input, stage output): Q1 = Q + dt L(Q); Q2 = 3/4 Q + 1/4 (Q1 + dt L(Q1));
     // Q <- 1/3 Q + 2/3 (Q2 + dt L(Q2))
     const double a0[3] = {0.0, 0.75, 1.0 / 3.0}, a1[3] = {1.0, 0.25, 2.0 / 3.0};
-    ns_class(g, [&](auto nsrc) {
-        constexpr int NSR = decltype(nsrc)::value;
-        if constexpr (NSR > 0) {
+    ns_class(g, [&](auto nc, auto widec) {
+        constexpr int N = decltype(nc)::value;
+        constexpr bool WIDE = decltype(widec)::value;
+        hipLaunchKernelGGL((fluid_prim_kernel<WIDE ? 0 : N>), dim3(gc), dim3(block), 0, s, t, g, Q, W, T);
+        if constexpr (N > 0) {
             // Q2 takes the place of the fluxes; the primitives alternate between two sets of rows
             double *const buf[3] = {Q, Q1, F}, *const prim[2] = {W, W + (size_t)3 * g.n};
-            hipLaunchKernelGGL((fluid_prim_kernel<NSR>), dim3(gc), dim3(block), 0, s, t, g, Q, prim[0], T);
-            int w = 0;
-            for (int sweep = 0; sweep < 2; ++sweep) {
-                const bool along_x = (sweep == 0) != y_first;
+            for (int k = 0; k < 6; ++k) {
+                const bool along_x = (k < 3) != y_first;
+                const double *in = buf[k % 3];
+                double *out = buf[(k + 1) % 3];
                 const double r = dt / (along_x ? dx : dy);
-                for (int k = 0; k < 3; ++k, w ^= 1) {
-                    const double *in = buf[k];
-                    double *out = buf[(k + 1) % 3];
-                    const bool last = sweep == 1 && k == 2;   // no stage reads its primitives
-                    if (along_x) {
-                        const long long waves = ((long long)(g.nx + 1) * g.ny + 62) / 63;
-                        const unsigned gx = (unsigned)((waves + 3) / 4);
-                        if (last)
-                            hipLaunchKernelGGL((fluid_stage_x_kernel<NSR, false>), dim3(gx), dim3(block), 0, s, t, g, Q, in, out,
-                                               prim[w], prim[w ^ 1], T, r, a0[k], a1[k]);
-                        else
-                            hipLaunchKernelGGL((fluid_stage_x_kernel<NSR, true>), dim3(gx), dim3(block), 0, s, t, g, Q, in, out,
-                                               prim[w], prim[w ^ 1], T, r, a0[k], a1[k]);
-                    } else {
-                        const int rows = rows_per_thread(g);
-                        const long long threads = (long long)g.nx * ((g.ny + rows - 1) / rows);
-                        const unsigned gy = (unsigned)((threads + block - 1) / block);
-                        if (last)
-                            hipLaunchKernelGGL((fluid_stage_y_kernel<NSR, false>), dim3(gy), dim3(block), 0, s, t, g, Q, in, out,
-                                               prim[w], prim[w ^ 1], T, r, a0[k], a1[k], rows);
-                        else
-                            hipLaunchKernelGGL((fluid_stage_y_kernel<NSR, true>), dim3(gy), dim3(block), 0, s, t, g, Q, in, out,
-                                               prim[w], prim[w ^ 1], T, r, a0[k], a1[k], rows);
-                    }
-                }
+                if (k < 5)
+                    launch_stage<N, WIDE, true>(t, g, along_x, Q, in, out, prim[k & 1], prim[~k & 1], T, r, a0[k % 3], a1[k % 3], s);
+                else   // no stage reads its primitives
+                    launch_stage<N, WIDE, false>(t, g, along_x, Q, in, out, prim[k & 1], prim[~k & 1], T, r, a0[k % 3], a1[k % 3], s);
             }
         } else {
-            // larger mixtures: a stage is its faces' kernel, then the update's, which in the first two
-            // stages also forms the primitives of its output
-            auto sweep = [&](auto dirc) {
+            // a stage is its faces' kernel, then the update's, which but for the step's last also forms the
+            // primitives of its output
+            auto sweep = [&](auto dirc, bool last_sweep) {
                 constexpr int D = decltype(dirc)::value;
                 const long long nf = D == 0 ? (long long)(g.nx + 1) * g.ny : (long long)g.nx * (g.ny + 1);
                 const unsigned gf = (unsigned)((nf + block - 1) / block);
                 const double r = dt / (D == 0 ? dx : dy);
-                hipLaunchKernelGGL((fluid_prim_kernel<0>), dim3(gc), dim3(block), 0, s, t, g, Q, W, T);
                 for (int k = 0; k < 3; ++k) {
                     const double *in = k == 0 ? Q : Q1;
+                    double *out = k == 2 ? Q : Q1;
                     hipLaunchKernelGGL((fluid_flux_kernel<D>), dim3(gf), dim3(block), 0, s, t, g, in, W, F);
-                    if (k == 2)
-                        hipLaunchKernelGGL((fluid_update_kernel<D, false>), dim3(gc), dim3(block), 0, s, t, g, Q, in, Q, F, r,
+                    if (k == 2 && last_sweep)
+                        hipLaunchKernelGGL((fluid_update_kernel<D, false>), dim3(gc), dim3(block), 0, s, t, g, Q, in, out, F, r,
                                            a0[k], a1[k], W, T);
                     else
-                        hipLaunchKernelGGL((fluid_update_kernel<D, true>), dim3(gc), dim3(block), 0, s, t, g, Q, in, Q1, F, r,
+                        hipLaunchKernelGGL((fluid_update_kernel<D, true>), dim3(gc), dim3(block), 0, s, t, g, Q, in, out, F, r,
                                            a0[k], a1[k], W, T);
                 }
             };
-            if (y_first) sweep(std::integral_constant<int, 1>{});
-            sweep(std::integral_constant<int, 0>{});
-            if (!y_first) sweep(std::integral_constant<int, 1>{});
+            if (y_first) sweep(std::integral_constant<int, 1>{}, false);
+            sweep(std::integral_constant<int, 0>{}, y_first);
+            if (!y_first) sweep(std::integral_constant<int, 1>{}, true);
         }
     });
     return hipGetLastError();
@@ -683,9 +923,10 @@ hipError_t launch_fluid_speed(const WaveTables &t, const FluidGrid &fg, const do
     const Grid g{t.ns, fg.nx, fg.ny, fg.bc, (long long)fg.nx * fg.ny};
     const int block = 256;
     const unsigned gc = (unsigned)((g.n + block - 1) / block);
-    ns_class(g, [&](auto nsrc) {
-        constexpr int NSR = decltype(nsrc)::value;
-        hipLaunchKernelGGL((fluid_prim_kernel<NSR>), dim3(gc), dim3(block), 0, s, t, g, Q, W, T);
+    ns_class(g, [&](auto nc, auto widec) {
+        constexpr int N = decltype(nc)::value;
+        constexpr bool WIDE = decltype(widec)::value;
+        hipLaunchKernelGGL((fluid_prim_kernel<WIDE ? 0 : N>), dim3(gc), dim3(block), 0, s, t, g, Q, W, T);
     });
     const long long sb = (g.n + kSpeedThreads - 1) / kSpeedThreads;
     hipLaunchKernelGGL(fluid_speed_kernel, dim3((unsigned)(sb < kSpeedBlocks ? sb : kSpeedBlocks)), dim3(kSpeedThreads),

@@ -1,6 +1,6 @@
 """GPU parity of the fluid step for mixtures whose species switch NASA-7 range at temperatures of
 their own, inside the flow's range: wavefronts whose lanes lie above every switch, below every switch
-or on both sides, at species counts around the compiled ones (up to 16) and streamed (17 and up).
+or on both sides, at species counts that a lane holds (up to 16), that four wavefronts share (17 to 64) and streamed.
 Gate: 1e-10 of each conserved variable's scale, as for the other fluid parity tests (two steps of
 FP64 arithmetic in another order: some 1e3 roundings of 1e-16 at most)."""
 import dataclasses
@@ -33,7 +33,7 @@ def two_range(ns, seed):
 
 
 @pytest.mark.parametrize("ns,bc,T", [(5, 1, (500.0, 1800.0)), (16, 0, (500.0, 1800.0)), (17, 1, (500.0, 1800.0)),
-                                     (40, 0, (500.0, 1800.0)), (9, 0, (400.0, 850.0)), (9, 1, (1400.0, 2500.0))])
+                                     (40, 0, (500.0, 1800.0)), (64, 1, (500.0, 1800.0)), (65, 0, (500.0, 1800.0)), (9, 0, (400.0, 850.0)), (9, 1, (1400.0, 2500.0))])
 def test_fluid_steps_two_ranges(ns, bc, T):
     from oracle import fluid_oracle as fo
     from paper_1110_4903_amd import kin
@@ -56,14 +56,15 @@ def test_fluid_steps_two_ranges(ns, bc, T):
         assert np.all(d <= 1e-10), d
 
 
-@pytest.mark.parametrize("nx,ny,bc", [(1, 1, 1), (1, 70, 1), (62, 3, 0), (63, 5, 1), (64, 4, 0), (125, 3, 1), (127, 3, 0),
-                                      (641, 410, 1), (1030, 1031, 0)])
-def test_fluid_step_tiles(nx, ny, bc):
-    """Row lengths around the 63 cells of a wavefront, fewer cells than a wavefront has, and columns that a
-    thread walks over several rows with a ragged last run."""
+@pytest.mark.parametrize("ns", [4, 19])
+@pytest.mark.parametrize("nx,ny,bc", [(1, 1, 1), (1, 70, 1), (3, 64, 0), (7, 9, 1), (62, 3, 0), (63, 5, 1), (64, 7, 0), (125, 3, 1),
+                                      (127, 8, 0), (641, 410, 1)])
+def test_fluid_step_tiles(nx, ny, bc, ns):
+    """Row lengths around the 63 cells of a wavefront and fewer cells than a wavefront has, widths and
+    heights around the tile of 8 columns and 7 cells, and a ragged grid of many tiles."""
     from oracle import fluid_oracle as fo
     from paper_1110_4903_amd import kin
-    m = two_range(4, 7)
+    m = two_range(ns, 7)
     gas = fo.Gas(m)
     dx, dy = 1e-3 / nx, 1e-3 / ny
     Q = np.ascontiguousarray(flow_state(fo, gas, nx, ny, 3, 500.0, 1800.0))
