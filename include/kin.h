@@ -54,7 +54,8 @@ typedef enum { KIN_MEM_HOST = 0, KIN_MEM_DEVICE = 1, KIN_MEM_PINNED = 2 } kin_me
  * per 64-wide wavefront with one matrix row per lane and the Jacobian staged in LDS
  * (ns <= 63), or one cell per wavefront with the cell's whole matrix in global memory, which
  * is what the paper's first kinetics kernel keeps there (Sec. 4.2; any ns up to 255, the
- * automatic choice above 63).  The global layout allocates its workspace (at most 16 GiB)
+ * automatic choice above 63; FP64 advances of 64 to 126 species in it take a workgroup per cell and
+ * keep the matrix in registers).  The global layout allocates its workspace (at most 16 GiB)
  * stream-ordered on the launch stream, or with the graph of a batched advance, and is bound
  * by HBM bandwidth. */
 typedef enum { KIN_LAYOUT_AUTO = 0, KIN_LAYOUT_LANE = 1, KIN_LAYOUT_WAVE = 2, KIN_LAYOUT_GLOBAL = 3 } kin_layout;

@@ -7,7 +7,8 @@
 // its columns, and factored by a blocked elimination that reads and writes each trailing
 // column once per panel of pivot steps.  The matrices of a launch live in a workspace of
 // slots, one per wavefront; a wavefront that finishes its cell takes the next from the work
-// counter.
+// counter.  FP64 advances of 64 to 126 species do not come here but to kin_block.hip, which keeps a
+// cell's matrix on chip.
 //
 // Method as in the other layouts: Newton iterations on backward Euler in x = (Y, T) for a
 // constant-(rho, e) cell, (I - hJ) dx = -G, dyadic sub-step halving on failure (Sec. 3.2,

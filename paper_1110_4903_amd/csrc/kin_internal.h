@@ -131,6 +131,34 @@ struct WaveTables {
                             // pass of 64 reactions
 };
 
+// Workgroup-per-cell kernel (kin_block.hip): wavefronts of a block, and columns of the Jacobian that it
+// builds at a time.
+constexpr int kBlockWaves = 8, kBlockStrip = 32, kBlockAhead = 4;   // kBlockAhead: records read ahead
+constexpr int kBlockNsMin = kWaveNsMax + 1, kBlockNsMax = 126;
+
+// Its tables.  The entries (s, k) of a strip's columns, species rows, with the values of the reactions that
+// add to them (columns 0..ns-1, T in column ns, the production in column ns + 1): 64 entries of similar
+// length form a group, one per lane, and the groups are dealt to the wavefronts, each of which reads one
+// stream of records of 64 x 16 bytes.  A group's first record has for each lane the entry's place in the
+// strip (0xffff: none) and seven terms, its further ones eight terms; a term is the byte offset of one
+// of the reactions' values with its sign in the lowest bit, padded with the offset of a zero.
+struct BlockTables {
+    bool on;                // the mechanism takes this kernel
+    int rmax, pmax, slots;  // largest reactant and product counts, and their sum
+    const int *gfirst;      // [strips * kBlockWaves + 1] first record of (strip, wavefront)
+    const int *gterms;      // [records] places in use | 0x100 on the first, 0x200 on the last of a group
+    const uint4 *rec;       // some unused ones at the end, which are read ahead
+    const double *iM;       // [ns] 1 / M
+    const double *effQ;     // [strips][ntb][kBlockStrip] eff_qk / M_k (a strip's part fits the vector cache)
+    // third-body entries (row s, slot q, nu_sq) in fours of one row, padded with factors of zero.  Rows with
+    // equally many fours go in pairs, a half-wavefront each, and the pairs are dealt to the wavefronts.
+    int nquad;
+    const int *qfirst;                  // [kBlockWaves + 1] first pair of fours of a wavefront, multiples of kBlockAhead
+    const int *qrow;                    // [nquad] rows (8 bits each, 0xff: none), bit 16 on the last fours of a pair
+    const int *qslot;                   // [nquad * 2 * 4]
+    const double *qnu;                  // [nquad * 2 * 4]
+};
+
 // Device layout of one instance's arena (n cells, ns species), from its base address:
 //   rho[n] e0[n] T[n] Y[ns][n] sched[n] (8-byte entries, each array 256-byte aligned)
 //   status[n] level[n] iters[n] (4-byte entries), one 64-bit work counter, the cell order
@@ -247,6 +275,9 @@ hipError_t launch_conserved_in(const WaveTables &t, long long n, long long ld, d
 hipError_t launch_conserved_out(const WaveTables &t, long long n, long long ld, const double *rho,
                                 const double *Y, const double *e0, double *rho_s, double *E_sens,
                                 hipStream_t s);
+// Workgroup-per-cell kernel (kin_block.hip), one block per cell of the launch, and the LDS of a block.
+size_t block_lds_bytes(const WaveTables &t, const BlockTables &b);
+hipError_t launch_block(const WaveTables &t, const BlockTables &b, const AdvanceArgs &a, hipStream_t stream);
 // Global-memory layout (kin_global.hip): workspace doubles per slot, and the launch over
 // `slots` threads with a workspace of slots * global_work_doubles_per_slot doubles.
 size_t global_work_doubles_per_slot(int ns, int ntb);

@@ -27,6 +27,7 @@ struct Mech {
     void *dbuf = nullptr;
     size_t dbytes = 0;
     WaveTables tab{};
+    BlockTables blk{};       // blk.on: FP64 advances in the global layout run the workgroup-per-cell kernel
     int layout = KIN_LAYOUT_WAVE;
     int block = 64;          // lane layout: threads per block; wave layout: waves per block
     hipModule_t mod = nullptr;
@@ -341,6 +342,15 @@ static kin_status build_lane_trace(kin_ctx *ctx, Mech &m, int block)
     return KIN_OK;
 }
 
+// The workgroup-per-cell kernel replaces the global layout's FP64 one wherever it can hold a cell: 64 to 126
+// species (two rows and sixteen columns of the matrix per lane), the reactions' values within 16 bits of index, and a block
+// within the 160 KB of a compute unit.
+constexpr size_t kBlockLdsMax = 160 * 1024 - 512;
+static bool uses_block(const Mech &m, int layout, int prec)
+{
+    return m.blk.on && layout == KIN_LAYOUT_GLOBAL && prec == KIN_FP64;
+}
+
 // Pack the device tables of the table-driven kernels.
 static kin_status upload_tables(kin_ctx *ctx, Mech &m)
 {
@@ -506,6 +516,124 @@ static kin_status upload_tables(kin_ctx *ctx, Mech &m)
             }
     }
     if (tgs.empty()) { tgs.push_back(0); tgf.push_back(0.0); }
+    // workgroup-per-cell kernel: the third-body entries by row, and the terms of the Jacobian's entries
+    BlockTables bt{};
+    std::vector<double> iM(ns), effQ, qnu;
+    std::vector<int> qfirst, qslot, qrow, gfirst, gterms;
+    std::vector<uint16_t> rec;
+    for (int s = 0; s < ns; ++s) iM[s] = 1.0 / h.M[s];
+    const int strips = (ns + 2 + kBlockStrip - 1) / kBlockStrip;
+    effQ.assign((size_t)strips * std::max(1, ntb) * kBlockStrip, 0.0);
+    for (int q = 0; q < ntb; ++q)
+        for (int k = 0; k < ns; ++k)
+            effQ[((size_t)(k / kBlockStrip) * ntb + q) * kBlockStrip + k % kBlockStrip] = effTM[(size_t)k * ntb + q];
+    for (const Rxn &x : h.rx) {
+        bt.rmax = std::max(bt.rmax, x.nreac);
+        bt.pmax = std::max(bt.pmax, x.nprod);
+    }
+    bt.slots = bt.rmax + bt.pmax;
+    {
+        // the rows' entries in fours, the longest row first to the group of lanes that has least
+        std::vector<std::vector<std::pair<int, double>>> rows(ns);
+        for (int r = 0; r < nr; ++r)
+            for (int j = 0; slot[r] >= 0 && j < h.rx[r].npart; ++j)
+                if (h.rx[r].part[j].nu) rows[h.rx[r].part[j].sp].push_back({slot[r], (double)h.rx[r].part[j].nu});
+        std::vector<int> by(ns);
+        for (int s = 0; s < ns; ++s) by[s] = s;
+        std::stable_sort(by.begin(), by.end(), [&](int a, int b) { return rows[a].size() > rows[b].size(); });
+        // pairs of equal length (a row without entries has one four of zeros), the longest first to the
+        // wavefront that has least
+        const auto fours = [&](int s) { return std::max<size_t>(1, (rows[s].size() + 3) / 4); };
+        std::vector<std::vector<int>> deal(kBlockWaves);   // places in by of a pair's first row
+        std::vector<size_t> load(kBlockWaves, 0);
+        for (int i = 0; i < ns; i += 2) {
+            const size_t w = std::min_element(load.begin(), load.end()) - load.begin();
+            deal[w].push_back(i);
+            load[w] += 1 + fours(by[i]);
+        }
+        qfirst.push_back(0);
+        for (int w = 0; w < kBlockWaves; ++w) {
+            for (int i : deal[w]) {
+                const size_t n = fours(by[i]);
+                const int s2[2] = {by[i], i + 1 < ns ? by[i + 1] : -1};
+                for (size_t e = 0; e < n; ++e) {
+                    for (int s : s2)
+                        for (size_t k = 4 * e; k < 4 * e + 4; ++k) {
+                            const bool in = s >= 0 && k < rows[s].size();
+                            qslot.push_back(in ? rows[s][k].first : 0);
+                            qnu.push_back(in ? rows[s][k].second : 0.0);
+                        }
+                    qrow.push_back(e + 1 == n ? (s2[0] & 0xff) | (s2[1] & 0xff) << 8 | 0x10000 : 0);
+                }
+            }
+            qrow.resize((qrow.size() + kBlockAhead - 1) / kBlockAhead * kBlockAhead, 0);
+            qslot.resize(8 * qrow.size(), 0);
+            qnu.resize(8 * qrow.size(), 0.0);
+            qfirst.push_back((int)qrow.size());
+        }
+        bt.nquad = (int)qrow.size();
+        WaveTables probe{};
+        probe.ns = ns; probe.nr = nr; probe.ntb = ntb;
+        bt.on = ns >= kBlockNsMin && ns <= kBlockNsMax && 8 * (size_t)(bt.slots + 2) * nr < 0xffff &&
+                block_lds_bytes(probe, bt) <= kBlockLdsMax;
+    }
+    if (bt.on) {
+        const uint16_t zero = (uint16_t)(8 * (bt.slots + 2) * nr);
+        const int nc = ns + 2;
+        std::vector<std::vector<uint16_t>> lists((size_t)ns * nc);
+        for (int i = 0; i < nr; ++i) {
+            const Rxn &x = h.rx[perm[i]];
+            
+            for (int a = 0; a < x.npart; ++a) {
+                const int nu = x.part[a].nu;
+                const auto value = [&](int v) { return (uint16_t)(8 * (v * nr + i) + (nu < 0 ? 1 : 0)); };
+                std::vector<uint16_t> *row = &lists[(size_t)x.part[a].sp * nc];
+                for (int rep = 0; rep < std::abs(nu); ++rep) {
+                    for (int q = 0; q < x.nreac; ++q) row[x.reac_sp[q]].push_back(value(q));
+                    for (int q = 0; q < x.nprod; ++q) row[x.prod_sp[q]].push_back(value(bt.rmax + q));
+                    row[ns + 1].push_back(value(bt.slots));       // q
+                    row[ns].push_back(value(bt.slots + 1));       // dq/dT
+                }
+            }
+        }
+        gfirst.push_back(0);
+        for (int st = 0; st < strips; ++st) {
+            std::vector<int> el;
+            for (int s = 0; s < ns; ++s)
+                for (int c = st * kBlockStrip; c < std::min(nc, (st + 1) * kBlockStrip); ++c)
+                    if (!lists[(size_t)s * nc + c].empty()) el.push_back(s * nc + c);
+            std::stable_sort(el.begin(), el.end(), [&](int a, int b) { return lists[a].size() > lists[b].size(); });
+            // the longest group first, to the wavefront that has least
+            std::vector<std::vector<size_t>> groups(kBlockWaves);
+            std::vector<size_t> load(kBlockWaves, 0);
+            for (size_t g = 0; g < el.size(); g += 64) {
+                const size_t w = std::min_element(load.begin(), load.end()) - load.begin();
+                groups[w].push_back(g);
+                load[w] += 8 + lists[el[g]].size();
+            }
+            for (int w = 0; w < kBlockWaves; ++w) {
+                for (size_t g : groups[w]) {
+                    const size_t n = lists[el[g]].size(), chunks = 1 + n / 8, at = rec.size();
+                    for (size_t k = 0; k < chunks; ++k)
+                        gterms.push_back((int)std::min<size_t>(8, n + 1 - 8 * k) | (k == 0 ? 0x100 : 0) | (k + 1 == chunks ? 0x200 : 0));
+                    rec.resize(at + chunks * 64 * 8, zero);
+                    for (int i = 0; i < 64; ++i) {
+                        uint16_t *p = &rec[at + 8 * i];
+                        if (g + i >= el.size()) { p[0] = 0xffff; continue; }
+                        const int e = el[g + i], s = e / nc, c = e % nc;
+                        p[0] = (uint16_t)(s * (kBlockStrip + 1) + c - st * kBlockStrip);
+                        const std::vector<uint16_t> &l = lists[e];
+                        for (size_t k = 0; k < l.size(); ++k)   // the eighth value of the record and on: a chunk further
+                            rec[at + ((k + 1) / 8) * 64 * 8 + 8 * i + (k + 1) % 8] = l[k];
+                    }
+                }
+                gfirst.push_back((int)gterms.size());
+            }
+        }
+    }
+    if (gfirst.empty()) gfirst.push_back(0);
+    if (gterms.empty()) gterms.push_back(0);
+    rec.resize(rec.size() + 2 * kBlockAhead * 64 * 8, 0);
     // one allocation, 256-byte aligned pieces
     struct Piece { const void *src; size_t bytes; size_t off; };
     std::vector<Piece> pc = {
@@ -516,7 +644,11 @@ static kin_status upload_tables(kin_ctx *ctx, Mech &m)
         {tbB.data(), sizeof(double) * tbB.size(), 0}, {chunk_rp.data(), sizeof(int) * chunk_rp.size(), 0},
         {ef.data(), sizeof(double) * ns, 0}, {tgs.data(), sizeof(int) * tgs.size(), 0},
         {tgf.data(), sizeof(double) * tgf.size(), 0}, {effTM.data(), sizeof(double) * effTM.size(), 0},
-        {fl.data(), sizeof(double) * fl.size(), 0}};
+        {fl.data(), sizeof(double) * fl.size(), 0},
+        {gfirst.data(), sizeof(int) * gfirst.size(), 0}, {gterms.data(), sizeof(int) * gterms.size(), 0}, {rec.data(), sizeof(uint16_t) * rec.size(), 0},
+        {iM.data(), sizeof(double) * iM.size(), 0}, {effQ.data(), sizeof(double) * effQ.size(), 0},
+        {qfirst.data(), sizeof(int) * qfirst.size(), 0}, {qslot.data(), sizeof(qslot[0]) * qslot.size(), 0},
+        {qrow.data(), sizeof(int) * qrow.size(), 0}, {qnu.data(), sizeof(double) * qnu.size(), 0}};
     size_t total = 0;
     for (Piece &p : pc) { p.off = total; total = align256(total + p.bytes); }
     std::vector<char> host(total, 0);
@@ -530,6 +662,16 @@ static kin_status upload_tables(kin_ctx *ctx, Mech &m)
     t.tb_last = tb_last;
     t.Tsw_lo = Tsw_lo; t.Tsw_hi = Tsw_hi;
     t.fl = reinterpret_cast<const double *>(b + pc[14].off);
+    bt.gfirst = reinterpret_cast<const int *>(b + pc[15].off);
+    bt.gterms = reinterpret_cast<const int *>(b + pc[16].off);
+    bt.rec = reinterpret_cast<const uint4 *>(b + pc[17].off);
+    bt.iM = reinterpret_cast<const double *>(b + pc[18].off);
+    bt.effQ = reinterpret_cast<const double *>(b + pc[19].off);
+    bt.qfirst = reinterpret_cast<const int *>(b + pc[20].off);
+    bt.qslot = reinterpret_cast<const int *>(b + pc[21].off);
+    bt.qrow = reinterpret_cast<const int *>(b + pc[22].off);
+    bt.qnu = reinterpret_cast<const double *>(b + pc[23].off);
+    m.blk = bt;
     t.lnPaR = std::log(kPatmCgs / kRuCgs);
     t.nasa = reinterpret_cast<const double *>(b + pc[0].off);
     t.Tmid = reinterpret_cast<const double *>(b + pc[1].off);
@@ -1012,6 +1154,9 @@ static kin_status launch_spans(kin_ctx *ctx, Mech &m, AdvanceArgs &a, kin_precis
         a.K = m.kconst;
         void *params[] = {&a};
         KIN_HIP(ctx, hipModuleLaunchKernel(fn, (unsigned)grid, 1, 1, block, 1, 1, 0, st, params, nullptr));
+    } else if (uses_block(m, layout, prec)) {
+        if (a.total > 0x7fffffffLL) return err(KIN_EINVAL, "too many cells for one launch of this layout");
+        KIN_HIP(ctx, launch_block(m.tab, m.blk, a, st));
     } else if (layout == KIN_LAYOUT_GLOBAL) {
         const long long S = gslots > 0 ? std::min(gslots, global_slots(m, a.total)) : global_slots(m, a.total);
         if (gwork) {
