@@ -285,6 +285,9 @@ size_t global_work_doubles_per_slot(int ns, int ntb);
 // ocount[kOrderClasses * order_tiles(n)].  key: the iterations of the previous advance, or
 // with direct, cost classes 0..kOrderClasses-1 already.
 // clear (may be null): a work counter that the order's scan sets to zero on the way
+// Cost classes of n cells (at most 2^31 - 1) for a first advance of dt in the table-driven layouts (3 ns + ntb
+// doubles of LDS).
+hipError_t launch_cost_key(const WaveTables &t, const Arena &a, long long n, double dt, int *key, hipStream_t s);
 hipError_t launch_cost_order(const int *key, long long n, bool direct, int *order, int *ocount,
                               unsigned long long *clear, hipStream_t s);
 hipError_t launch_global(const WaveTables &t, const AdvanceArgs &a, bool fp32_lu, double *work,

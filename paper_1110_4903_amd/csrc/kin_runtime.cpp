@@ -58,10 +58,12 @@ struct Inst {
 };
 
 // Instances at least this large take their cells in cost order: about four times the cells
-// the layout keeps in flight (65536 lanes in the lane layout, a few thousand wavefronts in
-// the others); below that every cell starts almost at once and the order only costs.
-constexpr long long kOrderMinCells = 32768;
+// the lane layout keeps in flight (65536 lanes; the order also moves cells apart that share cache
+// lines), less than twice those of the others (about 2500 wavefronts, 512 workgroups); below that
+// every cell starts almost at once and the order only costs.  XXX
 constexpr long long kOrderMinLaneCells = 262144;
+constexpr long long kOrderMinCells = 4096;
+constexpr long long kOrderMinBlockCells = 1024;
 
 // Code objects already compiled in this process, keyed by their source.
 static std::mutex g_jit_mu;
@@ -521,18 +523,18 @@ static kin_status upload_tables(kin_ctx *ctx, Mech &m)
     std::vector<double> iM(ns), effQ, qnu;
     std::vector<int> qfirst, qslot, qrow, gfirst, gterms;
     std::vector<uint16_t> rec;
-    for (int s = 0; s < ns; ++s) iM[s] = 1.0 / h.M[s];
     const int strips = (ns + 2 + kBlockStrip - 1) / kBlockStrip;
-    effQ.assign((size_t)strips * std::max(1, ntb) * kBlockStrip, 0.0);
-    for (int q = 0; q < ntb; ++q)
-        for (int k = 0; k < ns; ++k)
-            effQ[((size_t)(k / kBlockStrip) * ntb + q) * kBlockStrip + k % kBlockStrip] = effTM[(size_t)k * ntb + q];
-    for (const Rxn &x : h.rx) {
-        bt.rmax = std::max(bt.rmax, x.nreac);
-        bt.pmax = std::max(bt.pmax, x.nprod);
-    }
-    bt.slots = bt.rmax + bt.pmax;
-    {
+    if (ns >= kBlockNsMin && ns <= kBlockNsMax) {
+        for (int s = 0; s < ns; ++s) iM[s] = 1.0 / h.M[s];
+        effQ.assign((size_t)strips * std::max(1, ntb) * kBlockStrip, 0.0);
+        for (int q = 0; q < ntb; ++q)
+            for (int k = 0; k < ns; ++k)
+                effQ[((size_t)(k / kBlockStrip) * ntb + q) * kBlockStrip + k % kBlockStrip] = effTM[(size_t)k * ntb + q];
+        for (const Rxn &x : h.rx) {
+            bt.rmax = std::max(bt.rmax, x.nreac);
+            bt.pmax = std::max(bt.pmax, x.nprod);
+        }
+        bt.slots = bt.rmax + bt.pmax;
         // the rows' entries in fours, the longest row first to the group of lanes that has least
         std::vector<std::vector<std::pair<int, double>>> rows(ns);
         for (int r = 0; r < nr; ++r)
@@ -574,7 +576,7 @@ static kin_status upload_tables(kin_ctx *ctx, Mech &m)
         bt.nquad = (int)qrow.size();
         WaveTables probe{};
         probe.ns = ns; probe.nr = nr; probe.ntb = ntb;
-        bt.on = ns >= kBlockNsMin && ns <= kBlockNsMax && 8 * (size_t)(bt.slots + 2) * nr < 0xffff &&
+        bt.on = 8 * (size_t)(bt.slots + 2) * nr < 0xffff &&
                 block_lds_bytes(probe, bt) <= kBlockLdsMax;
     }
     if (bt.on) {
@@ -1382,9 +1384,11 @@ kin_status kin_advance(kin_ctx *ctx, const int32_t *inst_ids, const double *dts,
     a.total = in.n;
     a.counter = in.counter;
     // cost order: cells that needed many iterations in the previous advance are taken first;
-    // in the lane layout a first advance orders by the source term's temperature change.  The
+    // a first advance orders by the source term's temperature change.  The
     // order's scan also clears the work counter; without an order a kernel of its own does
-    const long long order_min = layout == KIN_LAYOUT_LANE ? kOrderMinLaneCells : kOrderMinCells;
+    const long long order_min = layout == KIN_LAYOUT_LANE    ? kOrderMinLaneCells
+                                : uses_block(m, layout, prec) ? kOrderMinBlockCells
+                                                              : kOrderMinCells;
     if (!o.point_implicit && in.n >= order_min && in.n <= 0x7fffffffLL) {
         const Arena ar = arena_at(static_cast<char *>(in.buf), in.n, m.h.ns);
         if (in.iters_current) {
@@ -1397,6 +1401,10 @@ kin_status kin_advance(kin_ctx *ctx, const int32_t *inst_ids, const double *dts,
             void *params[] = {&a, &key};
             const long long grid = (in.n + block - 1) / block;
             KIN_HIP(ctx, hipModuleLaunchKernel(m.lane_cost, (unsigned)grid, 1, 1, block, 1, 1, 0, st, params, nullptr));
+            KIN_HIP(ctx, launch_cost_order(ar.okey, in.n, true, ar.order, ar.ocount, in.counter, st));
+            a.span[0].order = ar.order;
+        } else if (layout != KIN_LAYOUT_LANE && sizeof(double) * (size_t)(3 * m.tab.ns + m.tab.ntb) <= 65536) {
+            KIN_HIP(ctx, launch_cost_key(m.tab, ar, in.n, dts[0], ar.okey, st));
             KIN_HIP(ctx, launch_cost_order(ar.okey, in.n, true, ar.order, ar.ocount, in.counter, st));
             a.span[0].order = ar.order;
         }
