@@ -166,8 +166,9 @@ __device__ __forceinline__ void b_rates(const WaveTables &t, const BlockTables &
     const double T = L.XK[ns];
     const double iT = 1.0 / T, lT = log(T);
     const double rc = 1e-3 * rho, lPaRT = t.lnPaR - lT;
-    // species functions; partial sums of c_v and its derivative, one per wavefront
-    if (wid * 64 < ns) {
+    // species functions; partial sums of c_v and its derivative, one per wavefront (64 species leave the
+    // second of them a sum of nothing)
+    if (wid < RW) {
         double cvp = 0.0, dcvp = 0.0;
         if (tid < ns) {
             const BThermo th = b_thermo(t, tid, T, iT, lT);

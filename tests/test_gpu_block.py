@@ -22,7 +22,12 @@ def test_block_kernel_against_oracle(ns, tb):
     n = 6
     st = synth.uniform_cells(11, n, m.ns, 0.5)
     ref = om.advance(st.rho, st.T, st.Y, 2e-8, with_sched=True)
+    other = synth.make_mechanism(synth.MechRecipe("blk100", seed=77, n_elements=5, n_species=100, n_reactions=400,
+                                                  frac_third_body=0.2, frac_irreversible=0.3))
+    so = synth.uniform_cells(12, 600, other.ns, 0.5)
     with kin.Context(0) as c:
+        j = c.state_upload(c.mech_upload(other), so.rho, so.T, so.Y)
+        c.advance([j], [1e-10])   # leaves its values in the LDS of every compute unit
         i = c.state_upload(c.mech_upload(m), st.rho, st.T, st.Y)
         c.advance([i], [2e-8])
         T, Y, status, _, iters = c.download(i)[:5]
