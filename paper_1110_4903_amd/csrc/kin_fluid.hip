@@ -15,8 +15,8 @@
 //                and dt times the flux difference.
 // One kernel does a stage: a cell's two fluxes, its update and the primitives of its new state stay
 // in registers, and only the step's first primitives have a kernel of their own.  Up to 16 species a
-// lane does all of a face and a cell (fluid_stage_kernel), up to 64 four wavefronts share them
-// (fluid_wide_kernel).  Larger mixtures, and grids whose arrays exceed 32-bit offsets, do a stage in
+// lane does all of a face and a cell (fluid_stage_kernel); two wavefronts share them on small grids of
+// nine species and up, four from 17 to 64 species (fluid_wide_kernel).  Larger mixtures, and grids whose arrays exceed 32-bit offsets, do a stage in
 // two kernels, with the fluxes in memory.  Consecutive lanes take consecutive x, so an access of a
 // wavefront is a few contiguous runs of a row.  The six-cell stencil is read from the state and
 // primitive arrays, which neighbouring lanes share through the caches.
@@ -26,7 +26,7 @@
 // wavefronts per SIMD (208 registers: the six-cell loads of nine species in flight) hide the rest of
 // the latency incompletely, and a bound on the registers makes the compiler spill (three wavefronts:
 // 1.8 times the time).  36 species on 401 x 250 cells: 36 and 42 us, of 34 us of traffic that the
-// caches partly hold.  3750 cells of nine species: 8-9 us a stage, the latency of one wavefront.
+// caches partly hold.  3750 cells of nine species: 7 us a stage, the latency of one wavefront.
 // us a step, 1024 x 1024 of 9 / 75 x 50 of 9 / 401 x 250 of 36 species:
 //   1166 / 162 / 1111  a division and branches in each limiter, a selection of every coefficient per
 //                      lane, energies summed species by species
@@ -34,6 +34,7 @@
 //                      73-100 us on the large grid)
 //    777 /  67 /  468  one kernel a stage up to 16 species, along y a walk up the columns
 //    687 /  57 /  247  tiles along y, tiles to XCDs in contiguous parts, the wide form
+//    687 /  50 /  247  the wide form of two wavefronts on small grids
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -528,44 +529,45 @@ __global__ void __launch_bounds__(256) fluid_stage_kernel(WaveTables t, Grid g, 
         stage_update<NSR, PRIM>(t, g, 8u * ((unsigned)c.fy * g.nx + c.fx), F, Fr, Q0, Q, Qout, r, a0, a1, Wout, Tc);
 }
 
-// ---- A stage of larger mixtures: kWide wavefronts work on the same 64 faces (or cells), lane by lane,
+// ---- A stage of larger mixtures: NW wavefronts work on the same 64 faces (or cells), lane by lane,
 // each on its own run of at most NSG species, whose face states stay in its registers; sums over the
 // species go through LDS, and every wavefront then evaluates the face's (cell's) scalars for itself.
-constexpr int kWide = 4;
-
 // LDS of a block, [..][64 lanes].  The arrays of one union alternate: between two writes of it, and
 // between a write and the last reads of the other member, lies a barrier of the other union's exchange.
-struct WideShared {
+template <int NW> struct WideShared {
     union {
         struct {
-            double sum[kWide][4][64];    // face: rho and rho R of the left and the right state
+            double sum[NW][4][64];    // face: rho and rho R of the left and the right state
             double prim[3][2][64];       // the states of u, v, P
         } f;
         struct {
-            double sum[kWide][2][64];    // cell: rho and rho R
+            double sum[NW][2][64];    // cell: rho and rho R
             double var[3][64];           // momenta and energy
         } c;
     } a;
     union {
-        double e[kWide][4][64];          // face: energy and heat capacity of both states
-        double B[kWide][6][64];          // cell: coefficients of the mixture's energy
+        double e[NW][4][64];          // face: energy and heat capacity of both states
+        double B[NW][6][64];          // cell: coefficients of the mixture's energy
     } b;
 };
 
 // A wavefront's species are s0 .. s0 + NSG - 1; those from ns on are the last species with no density.
-template <int NSG> struct WideRun {
+template <int NSG, int NW> struct WideRun {
+    // Momenta and energy, and likewise u, v and P, are dealt from the last wavefront on, which may have fewer
+    // species; from 3 on there is none.
+    static constexpr int kExtra = (3 + NW - 1) / NW;
     int w, s0, ns;
     __device__ __forceinline__ int row(int j) const { return s0 + j < ns ? s0 + j : ns - 1; }
     __device__ __forceinline__ bool has(int j) const { return s0 + j < ns; }
-    // the variable that the wavefront has besides: a momentum or the energy (none in the others)
-    __device__ __forceinline__ int extra() const { return w < 3 ? w : 2; }
+    __device__ __forceinline__ int extra(int j) const { return NW - 1 - w + NW * j; }
+    __device__ __forceinline__ int extra_row(int j) const { return extra(j) < 3 ? extra(j) : 2; }
 };
 
-// Fluxes of the wavefront's species into F[0..NSG-1], of its momentum or energy into F[NSG].
-template <int DIR, int NSG>
-__device__ __forceinline__ void face_flux_wide(const WaveTables &t, const Grid &g, const WideRun<NSG> &run, int lane, int fx,
-                                               int fy, const double *Qs, const double *W, WideShared &sh,
-                                               double (&F)[NSG + 1])
+// Fluxes of the wavefront's species into F[0..NSG-1], of its momenta or energy behind them.
+template <int DIR, int NSG, int NW>
+__device__ __forceinline__ void face_flux_wide(const WaveTables &t, const Grid &g, const WideRun<NSG, NW> &run, int lane, int fx,
+                                               int fy, const double *Qs, const double *W, WideShared<NW> &sh,
+                                               double (&F)[NSG + WideRun<NSG, NW>::kExtra])
 {
     const int a = DIR == 0 ? fx : fy;
     const int len = DIR == 0 ? g.nx : g.ny;
@@ -581,8 +583,10 @@ __device__ __forceinline__ void face_flux_wide(const WaveTables &t, const Grid &
         L = mp5(v0, v1, v2, v3, v4);
         R = mp5(v5, v4, v3, v2, v1);
     };
-    double Ls[NSG], Rv[NSG], pl, pr;
-    recon(W + (size_t)run.extra() * n, pl, pr);
+    constexpr int EX = WideRun<NSG, NW>::kExtra;
+    double Ls[NSG], Rv[NSG], pl[EX], pr[EX];
+#pragma unroll
+    for (int j = 0; j < EX; ++j) recon(W + (size_t)run.extra_row(j) * n, pl[j], pr[j]);
 #pragma unroll
     for (int j = 0; j < NSG; ++j) {
         recon(Qs + (size_t)run.row(j) * n, Ls[j], Rv[j]);
@@ -603,14 +607,16 @@ __device__ __forceinline__ void face_flux_wide(const WaveTables &t, const Grid &
     A.sum[run.w][1][lane] = s1;
     A.sum[run.w][2][lane] = s2;
     A.sum[run.w][3][lane] = s3;
-    if (run.w < 3) {
-        A.prim[run.w][0][lane] = pl;
-        A.prim[run.w][1][lane] = pr;
-    }
+#pragma unroll
+    for (int j = 0; j < EX; ++j)
+        if (run.extra(j) < 3) {
+            A.prim[run.extra(j)][0][lane] = pl[j];
+            A.prim[run.extra(j)][1][lane] = pr[j];
+        }
     __syncthreads();
     double rL = 0.0, rR = 0.0, GL = 0.0, GR = 0.0;
 #pragma unroll
-    for (int k = 0; k < kWide; ++k) {
+    for (int k = 0; k < NW; ++k) {
         rL += A.sum[k][0][lane];
         rR += A.sum[k][1][lane];
         GL += A.sum[k][2][lane];
@@ -631,7 +637,7 @@ __device__ __forceinline__ void face_flux_wide(const WaveTables &t, const Grid &
     __syncthreads();
     double eL = 0.0, cvL = 0.0, eR = 0.0, cvR = 0.0;
 #pragma unroll
-    for (int k = 0; k < kWide; ++k) {
+    for (int k = 0; k < NW; ++k) {
         eL += sh.b.e[k][0][lane];
         cvL += sh.b.e[k][1][lane];
         eR += sh.b.e[k][2][lane];
@@ -640,33 +646,36 @@ __device__ __forceinline__ void face_flux_wide(const WaveTables &t, const Grid &
     const Hlle h = hlle(unL, unR, utL, utR, PL, PR, rL, rR, GL, GR, eL, eR, cvL, cvR);
 #pragma unroll
     for (int j = 0; j < NSG; ++j) F[j] = fma(Ls[j], h.aL, Rv[j] * h.aR);
-    F[NSG] = run.w == (DIR == 0 ? 0 : 1) ? h.un : (run.w == (DIR == 0 ? 1 : 0) ? h.ut : h.E);
+#pragma unroll
+    for (int j = 0; j < EX; ++j)
+        F[NSG + j] = run.extra(j) == (DIR == 0 ? 0 : 1) ? h.un : (run.extra(j) == (DIR == 0 ? 1 : 0) ? h.ut : h.E);
 }
 
 // stage_update for the wavefront's variables of a cell (active: of the grid, and this lane's), then, with
 // PRIM, its primitives: every wavefront iterates on the same sums, one stores T, u, v and P each.
-template <int NSG, bool PRIM>
-__device__ __forceinline__ void stage_update_wide(const WaveTables &t, const Grid &g, const WideRun<NSG> &run, int lane,
-                                                  bool active, unsigned o, const double (&Fl)[NSG + 1],
-                                                  const double (&Fr)[NSG + 1], const double *Q0, const double *Q,
+template <int NSG, int NW, bool PRIM>
+__device__ __forceinline__ void stage_update_wide(const WaveTables &t, const Grid &g, const WideRun<NSG, NW> &run, int lane,
+                                                  bool active, unsigned o, const double (&Fl)[NSG + WideRun<NSG, NW>::kExtra],
+                                                  const double (&Fr)[NSG + WideRun<NSG, NW>::kExtra], const double *Q0, const double *Q,
                                                   double *Qout, double r, double a0, double a1, double *W, double *Tc,
-                                                  WideShared &sh)
+                                                  WideShared<NW> &sh)
 {
     const long long n = g.n;
-    double qn[NSG + 1], q0[NSG + 1];
+    constexpr int EX = WideRun<NSG, NW>::kExtra;
+    double qn[NSG + EX], q0[NSG + EX];
 #pragma unroll
-    for (int j = 0; j < NSG + 1; ++j) {
-        const size_t v = j < NSG ? run.row(j) : run.ns + run.extra();
+    for (int j = 0; j < NSG + EX; ++j) {
+        const size_t v = j < NSG ? run.row(j) : run.ns + run.extra_row(j - NSG);
         qn[j] = ld(Q + v * n, o);
         q0[j] = ld(Q0 + v * n, o);
     }
     double T = 0.0;
     if constexpr (PRIM) T = ld(Tc, o);
 #pragma unroll
-    for (int j = 0; j < NSG + 1; ++j) {
+    for (int j = 0; j < NSG + EX; ++j) {
         qn[j] = fma(a0, q0[j], a1 * fma(r, Fl[j] - Fr[j], qn[j]));
-        const bool mine = j < NSG ? run.has(j) : run.w < 3;
-        const size_t v = j < NSG ? run.row(j) : run.ns + run.extra();
+        const bool mine = j < NSG ? run.has(j) : run.extra(j - NSG) < 3;
+        const size_t v = j < NSG ? run.row(j) : run.ns + run.extra_row(j - NSG);
         if (mine && active) st(Qout + v * n, o, qn[j]);
         if (j < NSG && !mine) qn[j] = 0.0;
     }
@@ -681,11 +690,13 @@ __device__ __forceinline__ void stage_update_wide(const WaveTables &t, const Gri
         auto &C = sh.a.c;
         C.sum[run.w][0][lane] = s0;
         C.sum[run.w][1][lane] = s1;
-        if (run.w < 3) C.var[run.w][lane] = qn[NSG];
+#pragma unroll
+        for (int j = 0; j < EX; ++j)
+            if (run.extra(j) < 3) C.var[run.extra(j)][lane] = qn[NSG + j];
         __syncthreads();
         double rho = 0.0, rR = 0.0;
 #pragma unroll
-        for (int k = 0; k < kWide; ++k) {
+        for (int k = 0; k < NW; ++k) {
             rho += C.sum[k][0][lane];
             rR += C.sum[k][1][lane];
         }
@@ -707,7 +718,7 @@ __device__ __forceinline__ void stage_update_wide(const WaveTables &t, const Gri
             for (int k = 0; k < 6; ++k) {
                 B[k] = 0.0;
 #pragma unroll
-                for (int q = 0; q < kWide; ++q) B[k] += sh.b.B[q][k][lane];
+                for (int q = 0; q < NW; ++q) B[k] += sh.b.B[q][k][lane];
             }
             range_interval<0>(t, run.ns, T, lo, hi);
             while (go && it < 60 && T >= lo && T < hi) {
@@ -720,35 +731,37 @@ __device__ __forceinline__ void stage_update_wide(const WaveTables &t, const Gri
         }
         if (active) {
             if (run.w == 0) st(Tc, o, T);
-            if (run.w == 1) st(W, o, u);
-            if (run.w == 2) st(W + n, o, v);
-            if (run.w == 3) st(W + 2 * n, o, rR * T);
+#pragma unroll
+            for (int j = 0; j < EX; ++j)
+                if (run.extra(j) < 3)
+                    st(W + (size_t)run.extra(j) * n, o, run.extra(j) == 0 ? u : (run.extra(j) == 1 ? v : rR * T));
         }
     }
 }
 
-template <int NSG> __device__ __forceinline__ WideRun<NSG> wide_run(const Grid &g)
+template <int NSG, int NW> __device__ __forceinline__ WideRun<NSG, NW> wide_run(const Grid &g)
 {
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     return {w, w * NSG, g.ns};
 }
 
 // fluid_stage_kernel with a block per 64 faces.
-template <int DIR, int NSG, bool PRIM>
-__global__ void __launch_bounds__(64 * kWide) fluid_wide_kernel(WaveTables t, Grid g, const double *Q0, const double *Q,
+template <int DIR, int NSG, int NW, bool PRIM>
+__global__ void __launch_bounds__(64 * NW) fluid_wide_kernel(WaveTables t, Grid g, const double *Q0, const double *Q,
                                                                 double *Qout, const double *Win, double *Wout, double *Tc,
                                                                 double r, double a0, double a1, int lw)
 {
-    __shared__ WideShared sh;
-    const WideRun<NSG> run = wide_run<NSG>(g);
+    __shared__ WideShared<NW> sh;
+    const WideRun<NSG, NW> run = wide_run<NSG, NW>(g);
+    constexpr int EX = WideRun<NSG, NW>::kExtra;
     const int lane = threadIdx.x & 63;
     const Tile c = stage_tile<DIR>(g, xcd_block(), lane, lw);
-    double F[NSG + 1], Fr[NSG + 1];
-    face_flux_wide<DIR, NSG>(t, g, run, lane, c.fx, c.fy, Q, Win, sh, F);
+    double F[NSG + EX], Fr[NSG + EX];
+    face_flux_wide<DIR, NSG, NW>(t, g, run, lane, c.fx, c.fy, Q, Win, sh, F);
 #pragma unroll
-    for (int j = 0; j < NSG + 1; ++j) Fr[j] = __shfl_down(F[j], c.next);
+    for (int j = 0; j < NSG + EX; ++j) Fr[j] = __shfl_down(F[j], c.next);
     const int x = c.fx < g.nx ? c.fx : g.nx - 1, y = c.fy < g.ny ? c.fy : g.ny - 1;
-    stage_update_wide<NSG, PRIM>(t, g, run, lane, c.active, 8u * ((unsigned)y * g.nx + x), F, Fr, Q0, Q, Qout, r, a0, a1, Wout,
+    stage_update_wide<NSG, NW, PRIM>(t, g, run, lane, c.active, 8u * ((unsigned)y * g.nx + x), F, Fr, Q0, Q, Qout, r, a0, a1, Wout,
                                  Tc, sh);
 }
 
@@ -815,20 +828,39 @@ __global__ void fluid_energy_back_kernel(Grid g, double *Q, const double *KE, co
     Q[(size_t)(g.ns + 2) * g.n + i] = Es[i] + KE[i];
 }
 
-// f(N, Wide): up to kFluidNsRegs species the kernels compiled for N of them; up to kWide times as many
-// those of a block's wavefronts that take N each; else (or where 32-bit offsets do not reach) N = 0, the
-// streamed kernels
+// f(N, NW): up to kFluidNsRegs species the kernels compiled for N of them (NW = 1), from nine on in small
+// grids those of two wavefronts that take at most N each; up to 64 species those of four; else (or where
+// 32-bit offsets do not reach) N = 0, the streamed kernels.
+// Two wavefronts shorten a face's chain and cost more in all.  Nine species, us a step with one and with two:
+// 3750 cells 54.8 and 47.4, 15000 cells 55.3 and 51.3, 25200 cells 56.6 and 55.6, 51200 cells 60.7 and 66.2,
+// 2^20 cells 701 and 717.
+constexpr long long kFluidSmall = 16384;
 template <int N = 1, typename Fn>
 void ns_class(const Grid &g, Fn f)
 {
+    using std::integral_constant;
     if constexpr (N > kFluidNsRegs) {
-        f(std::integral_constant<int, 0>{}, std::false_type{});
+        f(integral_constant<int, 0>{}, integral_constant<int, 1>{});
     } else {
-        const bool small = g.n < (1ll << 29);
-        if (small && g.ns == N) f(std::integral_constant<int, N>{}, std::false_type{});
-        else if (N * kWide > kFluidNsRegs && small && g.ns > kFluidNsRegs && (g.ns + kWide - 1) / kWide == N) {
-            if constexpr (N * kWide > kFluidNsRegs) f(std::integral_constant<int, N>{}, std::true_type{});
-        } else ns_class<N + 1>(g, f);
+        const bool reach = g.n < (1ll << 29), two = g.n <= kFluidSmall && g.ns >= 9 && g.ns <= 16;
+        if (reach && !two && g.ns == N) return f(integral_constant<int, N>{}, integral_constant<int, 1>{});
+        if constexpr (N >= 5 && N <= 8)
+            if (two && (g.ns + 1) / 2 == N) return f(integral_constant<int, N>{}, integral_constant<int, 2>{});
+        if constexpr (N >= 5)
+            if (reach && g.ns > 16 && (g.ns + 3) / 4 == N) return f(integral_constant<int, N>{}, integral_constant<int, 4>{});
+        ns_class<N + 1>(g, f);
+    }
+}
+
+// Primitives of Q by the kernel compiled for the species count, up to 16, or the streamed one.
+template <int N = 1>
+void launch_prim(const WaveTables &t, const Grid &g, const double *Q, double *W, double *T, hipStream_t s)
+{
+    if constexpr (N > 16) {
+        hipLaunchKernelGGL(fluid_prim_kernel<0>, dim3((unsigned)((g.n + 255) / 256)), dim3(256), 0, s, t, g, Q, W, T);
+    } else {
+        if (g.ns != N || g.n >= (1ll << 29)) return launch_prim<N + 1>(t, g, Q, W, T, s);
+        hipLaunchKernelGGL(fluid_prim_kernel<N>, dim3((unsigned)((g.n + 255) / 256)), dim3(256), 0, s, t, g, Q, W, T);
     }
 }
 
@@ -839,7 +871,7 @@ void ns_class(const Grid &g, Fn f)
 constexpr int kTileLog = 3;
 
 // One stage, its input's primitives in Win and its output's to Wout (PRIM).
-template <int N, bool WIDE, bool PRIM>
+template <int N, int NW, bool PRIM>
 void launch_stage(const WaveTables &t, const Grid &g, bool along_x, const double *Q0, const double *Q, double *Qout,
                   const double *Win, double *Wout, double *T, double r, double a0, double a1, hipStream_t s)
 {
@@ -848,13 +880,13 @@ void launch_stage(const WaveTables &t, const Grid &g, bool along_x, const double
     const int height = 64 >> lw;
     const long long waves = along_x ? ((long long)(g.nx + 1) * g.ny + 62) / 63
                                     : (long long)((g.nx + (1 << lw) - 1) >> lw) * ((g.ny + height - 2) / (height - 1));
-    const dim3 block(WIDE ? 64 * kWide : 256), grid((unsigned)(((WIDE ? waves : (waves + 3) / 4) + 7) / 8 * 8));
+    const dim3 block(NW > 1 ? 64 * NW : 256), grid((unsigned)(((NW > 1 ? waves : (waves + 3) / 4) + 7) / 8 * 8));
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, grid, block, 0, s, t, g, Q0, Q, Qout, Win, Wout, T, r, a0, a1, lw);
     };
-    if constexpr (WIDE) {
-        if (along_x) go(fluid_wide_kernel<0, N, PRIM>);
-        else go(fluid_wide_kernel<1, N, PRIM>);
+    if constexpr (NW > 1) {
+        if (along_x) go(fluid_wide_kernel<0, N, NW, PRIM>);
+        else go(fluid_wide_kernel<1, N, NW, PRIM>);
     } else {
         if (along_x) go(fluid_stage_kernel<0, N, PRIM>);
         else go(fluid_stage_kernel<1, N, PRIM>);
@@ -872,10 +904,10 @@ hipError_t launch_fluid_step(const WaveTables &t, const FluidGrid &fg, double dt
     // (a0, a1, stage input, stage output): Q1 = Q + dt L(Q); Q2 = 3/4 Q + 1/4 (Q1 + dt L(Q1));
     // Q <- 1/3 Q + 2/3 (Q2 + dt L(Q2))
     const double a0[3] = {0.0, 0.75, 1.0 / 3.0}, a1[3] = {1.0, 0.25, 2.0 / 3.0};
-    ns_class(g, [&](auto nc, auto widec) {
+    ns_class(g, [&](auto nc, auto nwc) {
         constexpr int N = decltype(nc)::value;
-        constexpr bool WIDE = decltype(widec)::value;
-        hipLaunchKernelGGL((fluid_prim_kernel<WIDE ? 0 : N>), dim3(gc), dim3(block), 0, s, t, g, Q, W, T);
+        constexpr int NW = decltype(nwc)::value;
+        launch_prim(t, g, Q, W, T, s);
         if constexpr (N > 0) {
             // Q2 takes the place of the fluxes; the primitives alternate between two sets of rows
             double *const buf[3] = {Q, Q1, F}, *const prim[2] = {W, W + (size_t)3 * g.n};
@@ -885,9 +917,9 @@ hipError_t launch_fluid_step(const WaveTables &t, const FluidGrid &fg, double dt
                 double *out = buf[(k + 1) % 3];
                 const double r = dt / (along_x ? dx : dy);
                 if (k < 5)
-                    launch_stage<N, WIDE, true>(t, g, along_x, Q, in, out, prim[k & 1], prim[~k & 1], T, r, a0[k % 3], a1[k % 3], s);
+                    launch_stage<N, NW, true>(t, g, along_x, Q, in, out, prim[k & 1], prim[~k & 1], T, r, a0[k % 3], a1[k % 3], s);
                 else   // no stage reads its primitives
-                    launch_stage<N, WIDE, false>(t, g, along_x, Q, in, out, prim[k & 1], prim[~k & 1], T, r, a0[k % 3], a1[k % 3], s);
+                    launch_stage<N, NW, false>(t, g, along_x, Q, in, out, prim[k & 1], prim[~k & 1], T, r, a0[k % 3], a1[k % 3], s);
             }
         } else {
             // a stage is its faces' kernel, then the update's, which but for the step's last also forms the
@@ -923,11 +955,7 @@ hipError_t launch_fluid_speed(const WaveTables &t, const FluidGrid &fg, const do
     const Grid g{t.ns, fg.nx, fg.ny, fg.bc, (long long)fg.nx * fg.ny};
     const int block = 256;
     const unsigned gc = (unsigned)((g.n + block - 1) / block);
-    ns_class(g, [&](auto nc, auto widec) {
-        constexpr int N = decltype(nc)::value;
-        constexpr bool WIDE = decltype(widec)::value;
-        hipLaunchKernelGGL((fluid_prim_kernel<WIDE ? 0 : N>), dim3(gc), dim3(block), 0, s, t, g, Q, W, T);
-    });
+    launch_prim(t, g, Q, W, T, s);
     const long long sb = (g.n + kSpeedThreads - 1) / kSpeedThreads;
     hipLaunchKernelGGL(fluid_speed_kernel, dim3((unsigned)(sb < kSpeedBlocks ? sb : kSpeedBlocks)), dim3(kSpeedThreads),
                        0, s, t, g, Q, W, T, dx, dy, out);

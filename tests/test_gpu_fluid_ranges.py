@@ -56,12 +56,13 @@ def test_fluid_steps_two_ranges(ns, bc, T):
         assert np.all(d <= 1e-10), d
 
 
-@pytest.mark.parametrize("ns", [4, 19])
+@pytest.mark.parametrize("ns", [4, 9, 16, 19])
 @pytest.mark.parametrize("nx,ny,bc", [(1, 1, 1), (1, 70, 1), (3, 64, 0), (7, 9, 1), (62, 3, 0), (63, 5, 1), (64, 7, 0), (125, 3, 1),
-                                      (127, 8, 0), (641, 410, 1)])
+                                      (127, 8, 0), (641, 410, 1), (128, 128, 0), (145, 113, 1)])
 def test_fluid_step_tiles(nx, ny, bc, ns):
     """Row lengths around the 63 cells of a wavefront and fewer cells than a wavefront has, widths and
-    heights around the tile of 8 columns and 7 cells, and a ragged grid of many tiles."""
+    heights around the tile of 8 columns and 7 cells, a ragged grid of many tiles, and the largest grid
+    of which two wavefronts share a face (16384 cells, from nine species on) with the next one."""
     from oracle import fluid_oracle as fo
     from paper_1110_4903_amd import kin
     m = two_range(ns, 7)
