@@ -25,7 +25,8 @@
 // two blocks: elimination 140 k (1390 cycles a pivot: LDS 200, the first column 100, search and reciprocal 600,
 // the other columns 400, of which a v_readlane_b32 takes ten cycles), third-body terms 37 k (4.5 rows use
 // each row of efficiencies, from the vector cache at 21 bytes a cycle), gathering 18 k, rates 20 k.  2048 cells
-// at 1 us: 57 ms, on one wavefront per cell with the matrix in global memory 127 ms.
+// at 1 us: 57 ms in index order, 47 ms in cost order; on one wavefront per cell with the matrix in global
+// memory 127 ms.
 // Measured and not taken: panels of four columns per barrier (5500 cycles a panel: the wavefront that has
 // factored one has its other columns still to do), pivot rows through LDS instead of v_readlane_b32 (LDS
 // bound), four wavefronts, a block of 256 registers a lane alone on its compute unit.

@@ -16,10 +16,11 @@
 // One kernel does a stage: a cell's two fluxes, its update and the primitives of its new state stay
 // in registers, and only the step's first primitives have a kernel of their own.  Up to 16 species a
 // lane does all of a face and a cell (fluid_stage_kernel); two wavefronts share them on small grids of
-// nine species and up, four from 17 to 64 species (fluid_wide_kernel).  Larger mixtures, and grids whose arrays exceed 32-bit offsets, do a stage in
-// two kernels, with the fluxes in memory.  Consecutive lanes take consecutive x, so an access of a
-// wavefront is a few contiguous runs of a row.  The six-cell stencil is read from the state and
-// primitive arrays, which neighbouring lanes share through the caches.
+// nine species and up, four from 17 to 64 species (fluid_wide_kernel).  Larger mixtures, and grids
+// whose arrays exceed 32-bit offsets, do a stage in two kernels, with the fluxes in memory.
+// Consecutive lanes take consecutive x, so an access of a wavefront is a few contiguous runs of a
+// row.  The six-cell stencil is read from the state and primitive arrays, which neighbouring lanes
+// share through the caches.
 //
 // What bounds it: a stage of nine species on 1024 x 1024 cells takes 107 us along x and 127 us along
 // y, where its 352 bytes a cell at the rate of a large copy (4.7 TB/s) would take 79 us; two
@@ -652,7 +653,7 @@ __device__ __forceinline__ void face_flux_wide(const WaveTables &t, const Grid &
 }
 
 // stage_update for the wavefront's variables of a cell (active: of the grid, and this lane's), then, with
-// PRIM, its primitives: every wavefront iterates on the same sums, one stores T, u, v and P each.
+// PRIM, its primitives: every wavefront iterates on the same sums, and they share the storing of T, u, v and P.
 template <int NSG, int NW, bool PRIM>
 __device__ __forceinline__ void stage_update_wide(const WaveTables &t, const Grid &g, const WideRun<NSG, NW> &run, int lane,
                                                   bool active, unsigned o, const double (&Fl)[NSG + WideRun<NSG, NW>::kExtra],
