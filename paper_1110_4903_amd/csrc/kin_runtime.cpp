@@ -59,12 +59,13 @@ struct Inst {
 
 // Instances at least this large take their cells in cost order: about four times the cells
 // the lane layout keeps in flight (65536 lanes; the order also moves cells apart that share cache
-// lines), less than twice those of the others (about 2500 wavefronts, 512 workgroups); below that
-// every cell starts almost at once and the order only costs.  16384 cells of 36 species take 38.0 ms in
-// index order and 31.7 ms in this, 2048 cells of 100 species 57 and 47 ms, 0.08 ms of it for the order.
+// lines), more than are in flight in the others (about 2500 wavefronts, 512 workgroups); below that
+// every cell starts at once and the order only costs its 0.06 to 0.08 ms.  In index order and in this, ms:
+// 36 species, 2700 cells 16.8 and 15.5, 3200 cells 16.8 and 14.5, 16384 cells (0.1 us) 38.0 and 31.7; 100 species,
+// 520 cells 23.2 and 22.5, 768 cells 32.3 and 22.5, 2048 cells 57 and 47.
 constexpr long long kOrderMinLaneCells = 262144;
-constexpr long long kOrderMinCells = 4096;
-constexpr long long kOrderMinBlockCells = 1024;
+constexpr long long kOrderMinCells = 2560;
+constexpr long long kOrderMinBlockCells = 513;
 
 // Code objects already compiled in this process, keyed by their source.
 static std::mutex g_jit_mu;

@@ -1,5 +1,5 @@
 """A first advance takes the cells of an instance in the order of their predicted cost from a size on that
-depends on the layout; the order never changes a cell.  Instances just above that size are compared bitwise
+depends on the layout; the order never changes a cell.  Instances at and above that size are compared bitwise
 with their cells advanced in small instances, which take them as they come, and with a second advance of the
 same states, which the first one's iteration counts order."""
 import numpy as np
@@ -10,8 +10,9 @@ from paper_1110_4903_amd import synth
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("which,n,part,dt,prec", [("mech36", 4100, 512, 1e-7, "fp64"), ("mech36", 4096, 1024, 1e-7, "fp32lu"),
-                                                  ("big", 1024, 128, 1e-8, "fp64"), ("big", 4097, 2000, 1e-9, "fp32lu")])
+@pytest.mark.parametrize("which,n,part,dt,prec", [("mech36", 2560, 512, 1e-7, "fp64"), ("mech36", 4097, 1024, 1e-7, "fp32lu"),
+                                                  ("big", 513, 128, 1e-8, "fp64"), ("big", 1400, 500, 1e-8, "fp64"),
+                                                  ("big", 2561, 2000, 1e-9, "fp32lu")])
 def test_first_advance_order_is_bitwise_neutral(which, n, part, dt, prec):
     from paper_1110_4903_amd import kin
     m = synth.mechanism("mech36") if which == "mech36" else synth.make_mechanism(synth.MechRecipe(
