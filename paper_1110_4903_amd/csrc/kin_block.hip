@@ -446,7 +446,7 @@ __device__ __forceinline__ void b_eliminate(const BLds &L, int N, int lane, int 
             L.ctl[kCtlPivot + (k & 1)] = row;
             L.rp[row] = rp;
             L.xof[row] = k;
-            if (best == 0) L.ctl[kCtlBad] = 1;
+            if (best == 0) L.ctl[kCtlBad] = 1;   // (row may have been a pivot before: what follows is not used)
         }
     };
     const auto step = [&](int k, int next, int left) {   // next: the wavefront of column k + 1, its first now
@@ -638,10 +638,14 @@ __global__ void __launch_bounds__(kBT, 4) block_kernel(WaveTables t, BlockTables
         b_eliminate<NC>(L, N, lane, wid, A);
         if (wid == cw) {
             double dx[RW], xk[RW];
+            // a column without a pivot leaves rows that were none either: their xof was never written
+            const bool ok = L.ctl[kCtlBad] == 0;
+            if (ok) {
 #pragma unroll
-            for (int m = 0; m < RW; ++m) {
-                const int i = lane + 64 * m;
-                if (i < N) L.dx[L.xof[i]] = A[m][0] * L.rp[i];
+                for (int m = 0; m < RW; ++m) {
+                    const int i = lane + 64 * m;
+                    if (i < N) L.dx[L.xof[i]] = A[m][0] * L.rp[i];
+                }
             }
             wave_sync();
 #pragma unroll
@@ -650,7 +654,6 @@ __global__ void __launch_bounds__(kBT, 4) block_kernel(WaveTables t, BlockTables
                 dx[m] = i < N ? L.dx[i] : 0.0;
                 xk[m] = i < N ? L.XK[i] : 0.0;
             }
-            const bool ok = L.ctl[kCtlBad] == 0;
             ++iters;
             if (k == 0) r_prev = -1.0;
             int outcome = 0;   // 0 go on, 1 accepted, 2 the attempt failed
