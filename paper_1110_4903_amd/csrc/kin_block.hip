@@ -560,18 +560,18 @@ template <typename... P> __device__ __forceinline__ void afresh(size_t z, P &...
     (..., (p += z));
 }
 
-// One block per cell; the hardware dispatcher balances cells of very different iteration counts.  The
-// wavefront with the right-hand side holds the cell's state and decides; ctl and sc tell the others whether
+// One block per cell, from the launch's cell `first` on; the hardware dispatcher balances cells of very
+// different iteration counts.  The wavefront with the right-hand side holds the cell's state and decides; ctl and sc tell the others whether
 // to go on and the sub-step size.
 template <int NC>
-__global__ void __launch_bounds__(kBT, 4) block_kernel(WaveTables t, BlockTables b, AdvanceArgs a)
+__global__ void __launch_bounds__(kBT, 4) block_kernel(WaveTables t, BlockTables b, AdvanceArgs a, long long first)
 {
     extern __shared__ double bsmem[];
     const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ns = t.ns, N = ns + 1;
     const BLds L(b_places(b, ns, t.nr, t.ntb), (lds_d *)bsmem);
     const int cw = N % kBW;   // the wavefront of column N
-    const long long gi = blockIdx.x;
+    const long long gi = first + blockIdx.x;
     if (gi >= a.total) return;
     int j = 0;
     while (j + 1 < a.nspan && a.span[j + 1].start <= gi) ++j;
@@ -773,14 +773,21 @@ static hipError_t launch_nc(size_t lds, const WaveTables &t, const BlockTables &
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&block_kernel<NC>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((block_kernel<NC>), dim3((unsigned)a.total), dim3(kBT), lds, s, t, b, a);
-    return hipGetLastError();
+    // a grid holds less than 2^32 threads, so the cells go in parts of half as many
+    constexpr long long kPart = (1ll << 31) / kBT;
+    for (long long first = 0; first < a.total; first += kPart) {
+        const long long n = a.total - first < kPart ? a.total - first : kPart;
+        hipLaunchKernelGGL((block_kernel<NC>), dim3((unsigned)n), dim3(kBT), lds, s, t, b, a, first);
+        const hipError_t le = hipGetLastError();
+        if (le != hipSuccess) return le;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_block(const WaveTables &t, const BlockTables &b, const AdvanceArgs &a, hipStream_t s)
 {
     if (a.total <= 0) return hipSuccess;
-    if (a.total > 0x7fffffffLL || t.ns < kBlockNsMin || t.ns > kBlockNsMax) return hipErrorInvalidValue;
+    if (t.ns < kBlockNsMin || t.ns > kBlockNsMax) return hipErrorInvalidValue;
     const size_t lds = block_lds_bytes(t, b);
     switch ((t.ns + 2 + kBlockStrip - 1) / kBlockStrip) {
     case 3: return launch_nc<3 * kStripLocal>(lds, t, b, a, s);

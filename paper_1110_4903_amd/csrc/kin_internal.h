@@ -275,7 +275,8 @@ hipError_t launch_conserved_in(const WaveTables &t, long long n, long long ld, d
 hipError_t launch_conserved_out(const WaveTables &t, long long n, long long ld, const double *rho,
                                 const double *Y, const double *e0, double *rho_s, double *E_sens,
                                 hipStream_t s);
-// Workgroup-per-cell kernel (kin_block.hip), one block per cell of the launch, and the LDS of a block.
+// Workgroup-per-cell kernel (kin_block.hip), one block per cell of the launch (any number of
+// them), and the LDS of a block.
 size_t block_lds_bytes(const WaveTables &t, const BlockTables &b);
 hipError_t launch_block(const WaveTables &t, const BlockTables &b, const AdvanceArgs &a, hipStream_t stream);
 // Global-memory layout (kin_global.hip): workspace doubles per slot, and the launch over

@@ -1159,7 +1159,6 @@ static kin_status launch_spans(kin_ctx *ctx, Mech &m, AdvanceArgs &a, kin_precis
         void *params[] = {&a};
         KIN_HIP(ctx, hipModuleLaunchKernel(fn, (unsigned)grid, 1, 1, block, 1, 1, 0, st, params, nullptr));
     } else if (uses_block(m, layout, prec)) {
-        if (a.total > 0x7fffffffLL) return err(KIN_EINVAL, "too many cells for one launch of this layout");
         KIN_HIP(ctx, launch_block(m.tab, m.blk, a, st));
     } else if (layout == KIN_LAYOUT_GLOBAL) {
         const long long S = gslots > 0 ? std::min(gslots, global_slots(m, a.total)) : global_slots(m, a.total);

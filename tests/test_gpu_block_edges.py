@@ -46,3 +46,36 @@ def test_block_kernel_singular_matrix(ns, a, b):
         c.advance([i], [dt], opts=kin.solver_opts(L_forced=0))
         T, Y, status = c.download(i)[:3]
         assert np.all(status == 2) and np.array_equal(T, st.T) and np.array_equal(Y, st.Y)
+
+
+def test_block_kernel_more_threads_than_a_grid_holds():
+    """2^23 cells are 2^32 threads: every cell advances, in the same way as in a small instance."""
+    import torch
+    from paper_1110_4903_amd import kin
+    ns, n = 64, (1 << 23) + 5
+    m = exchange_mech(ns, 0, 1)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    dev = dict(device="cuda", dtype=torch.float64)
+    T = 1000.0 + 2000.0 * torch.rand(n, generator=g, **dev)
+    rho = 0.1 + torch.rand(n, generator=g, **dev)
+    Y = torch.rand(ns, n, generator=g, **dev)
+    Y /= Y.sum(0)
+    pick = torch.cat([torch.arange(0, n, n // 50, device="cuda"), torch.arange(n - 6, n, device="cuda")])
+    dt = 0.25   # k dt = 1/4 each way: the difference shrinks by 1 + 2 k dt
+    torch.cuda.synchronize()
+    with kin.Context(0) as c:
+        mid = c.mech_upload(m)
+        i = c.state_upload(mid, rho, T, Y)
+        j = c.state_upload(mid, rho[pick].contiguous(), T[pick].contiguous(), Y[:, pick].contiguous())
+        c.advance([i], [dt])
+        c.advance([j], [dt])
+        T1, Y1 = torch.empty_like(T), torch.empty_like(Y)
+        status = torch.full((n,), -1, device="cuda", dtype=torch.int32)
+        c.download_device(i, T1, Y1, status=status)
+        c.sync()
+        assert int((status != 0).sum()) == 0
+        want = (Y[0] - Y[1]) / 1.5
+        assert float((Y1[0] - Y1[1] - want).abs().max()) <= 1e-14 and bool((Y1[2:] == Y[2:]).all())
+        part = c.download(j)
+        assert np.array_equal(part[0], T1[pick].cpu().numpy()) and np.array_equal(np.asarray(part[1]), Y1[:, pick].cpu().numpy())
