@@ -354,6 +354,11 @@ static bool uses_block(const Mech &m, int layout, int prec)
 {
     return m.blk.on && layout == KIN_LAYOUT_GLOBAL && prec == KIN_FP64;
 }
+// Launches whose matrices live in a workspace.
+static bool needs_workspace(const Mech &m, int layout, int prec)
+{
+    return layout == KIN_LAYOUT_GLOBAL && !uses_block(m, layout, prec);
+}
 
 // Pack the device tables of the table-driven kernels.
 static kin_status upload_tables(kin_ctx *ctx, Mech &m)
@@ -1280,7 +1285,7 @@ static kin_status advance_batch(kin_ctx *ctx, const int32_t *ids, const double *
             if (L.layout == KIN_LAYOUT_LANE) {
                 kin_status s = build_lane(ctx, *L.m, L.block);
                 if (s != KIN_OK) return s;
-            } else if (L.layout == KIN_LAYOUT_GLOBAL) {
+            } else if (needs_workspace(*L.m, L.layout, prec)) {
                 goff[q] = gtotal;
                 gtotal += global_work_doubles(*L.m, L.a.total);
             }
@@ -1299,7 +1304,7 @@ static kin_status advance_batch(kin_ctx *ctx, const int32_t *ids, const double *
             he = launch_zero_u64(ctx->counters + q, 1, sq);
             if (he != hipSuccess) break;
             cs = launch_spans(ctx, *launches[q].m, launches[q].a, prec, launches[q].layout, launches[q].block, sq,
-                              launches[q].layout == KIN_LAYOUT_GLOBAL ? gw + goff[q] : nullptr);
+                              needs_workspace(*launches[q].m, launches[q].layout, prec) ? gw + goff[q] : nullptr);
             if (cs == KIN_OK && q > 0) {
                 he = hipEventRecord(ctx->join[q], sq);
                 if (he == hipSuccess) he = hipStreamWaitEvent(c0, ctx->join[q], 0);
@@ -1506,7 +1511,7 @@ kin_status kin_advance_noalloc(kin_ctx *ctx, const int32_t *inst_ids, const doub
         if (L.layout == KIN_LAYOUT_LANE && !(L.m->mod && L.m->lane_block == L.block))
             return err(KIN_EINVAL, "the lane-layout kernels of this mechanism are not compiled for " +
                                        std::to_string(L.block) + " threads per block; kin_set_layout or kin_advance compiles them");
-        if (L.layout == KIN_LAYOUT_GLOBAL &&
+        if (needs_workspace(*L.m, L.layout, prec) &&
             sizeof(double) * global_work_doubles_per_slot(L.m->h.ns, L.m->tab.ntb) > work_bytes)
             return err(KIN_EINVAL, "one cell's matrix exceeds the fixed workspace");
     }
@@ -1516,9 +1521,10 @@ kin_status kin_advance_noalloc(kin_ctx *ctx, const int32_t *inst_ids, const doub
         L.a.counter = counters + q;
         KIN_HIP(ctx, launch_zero_u64(counters + q, 1, st));
         long long gslots = 0;
-        if (L.layout == KIN_LAYOUT_GLOBAL)  // launches are stream-ordered, so they share it
+        const bool ws = needs_workspace(*L.m, L.layout, prec);
+        if (ws)  // launches are stream-ordered, so they share it
             gslots = (long long)(work_bytes / (sizeof(double) * global_work_doubles_per_slot(L.m->h.ns, L.m->tab.ntb)));
-        s = launch_spans(ctx, *L.m, L.a, prec, L.layout, L.block, st, L.layout == KIN_LAYOUT_GLOBAL ? work : nullptr, gslots);
+        s = launch_spans(ctx, *L.m, L.a, prec, L.layout, L.block, st, ws ? work : nullptr, gslots);
         if (s != KIN_OK) return s;
     }
     for (int k = 0; k < n; ++k) ctx->insts[inst_ids[k]]->iters_current = true;

@@ -79,3 +79,25 @@ def test_block_kernel_more_threads_than_a_grid_holds():
         assert float((Y1[0] - Y1[1] - want).abs().max()) <= 1e-14 and bool((Y1[2:] == Y[2:]).all())
         part = c.download(j)
         assert np.array_equal(part[0], T1[pick].cpu().numpy()) and np.array_equal(np.asarray(part[1]), Y1[:, pick].cpu().numpy())
+
+
+def test_block_kernel_batch_holds_no_workspace():
+    """The graph of a batched advance holds the matrices of the one-wavefront kernel (1.6 GiB here); a workgroup
+    per cell keeps its own on chip, so the batch may take only what the runtime sets up for a graph."""
+    import torch
+    from paper_1110_4903_amd import kin
+    m = exchange_mech(100, 0, 1)
+    st = synth.uniform_cells(8, 8192, m.ns, 0.5)
+    with kin.Context(0) as c:
+        mid = c.mech_upload(m)
+        ids = [c.state_upload(mid, st.rho, st.T, st.Y) for _ in range(3)]
+        c.advance(ids[2:], [0.25])   # (the kernel's own set-up)
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        c.advance(ids[:2], [0.25, 0.25])
+        torch.cuda.synchronize()
+        assert free - torch.cuda.mem_get_info()[0] < 128 << 20
+        want = c.download(ids[2])
+        for i in ids[:2]:
+            for x, y in zip(c.download(i), want):
+                assert np.array_equal(x, y)
