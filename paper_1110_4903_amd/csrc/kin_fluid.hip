@@ -663,15 +663,27 @@ __device__ __forceinline__ void stage_update_wide(const WaveTables &t, const Gri
 {
     const long long n = g.n;
     constexpr int EX = WideRun<NSG, NW>::kExtra;
-    double qn[NSG + EX], q0[NSG + EX];
+    // Q0 and Tc of a cell belong to the lane that has it (Q0 is Qout in the last stage, and Tc is both read
+    // and written): the others read neither, and take an active lane's T so that the wavefront's choice of
+    // NASA-7 ranges stays the active lanes' own.
+    double qn[NSG + EX], q0[NSG + EX], T = 0.0;
+    if (active) {
 #pragma unroll
-    for (int j = 0; j < NSG + EX; ++j) {
-        const size_t v = j < NSG ? run.row(j) : run.ns + run.extra_row(j - NSG);
-        qn[j] = ld(Q + v * n, o);
-        q0[j] = ld(Q0 + v * n, o);
+        for (int j = 0; j < NSG + EX; ++j) {
+            const size_t v = j < NSG ? run.row(j) : run.ns + run.extra_row(j - NSG);
+            qn[j] = ld(Q + v * n, o);
+            q0[j] = ld(Q0 + v * n, o);
+        }
+        if constexpr (PRIM) T = ld(Tc, o);
+    } else {
+#pragma unroll
+        for (int j = 0; j < NSG + EX; ++j) qn[j] = q0[j] = 0.0;
     }
-    double T = 0.0;
-    if constexpr (PRIM) T = ld(Tc, o);
+    if constexpr (PRIM) {
+        const unsigned long long with = __ballot(active);
+        const double Ta = __shfl(T, with ? __builtin_ctzll(with) : 0);
+        if (!active) T = Ta;
+    }
 #pragma unroll
     for (int j = 0; j < NSG + EX; ++j) {
         qn[j] = fma(a0, q0[j], a1 * fma(r, Fl[j] - Fr[j], qn[j]));
