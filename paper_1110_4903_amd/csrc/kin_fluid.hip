@@ -855,12 +855,13 @@ void ns_class(const Grid &g, Fn f)
     if constexpr (N > kFluidNsRegs) {
         f(integral_constant<int, 0>{}, integral_constant<int, 1>{});
     } else {
-        const bool reach = g.n < (1ll << 29), two = g.n <= kFluidSmall && g.ns >= 9 && g.ns <= 16;
+        // (four wavefronts are up to 8.2 threads a cell, of which a grid holds less than 2^32)
+        const bool reach = g.n < (1ll << 29), reach4 = g.n < (1ll << 32) / 9, two = g.n <= kFluidSmall && g.ns >= 9 && g.ns <= 16;
         if (reach && !two && g.ns == N) return f(integral_constant<int, N>{}, integral_constant<int, 1>{});
         if constexpr (N >= 5 && N <= 8)
             if (two && (g.ns + 1) / 2 == N) return f(integral_constant<int, N>{}, integral_constant<int, 2>{});
         if constexpr (N >= 5)
-            if (reach && g.ns > 16 && (g.ns + 3) / 4 == N) return f(integral_constant<int, N>{}, integral_constant<int, 4>{});
+            if (reach4 && g.ns > 16 && (g.ns + 3) / 4 == N) return f(integral_constant<int, N>{}, integral_constant<int, 4>{});
         ns_class<N + 1>(g, f);
     }
 }
@@ -881,6 +882,9 @@ void launch_prim(const WaveTables &t, const Grid &g, const double *Q, double *W,
 // compute 8/7 of the faces and read 64 contiguous bytes at a time.  Nine species on 1024 x 1024 cells,
 // 36 on 401 x 250, us a step: width 4 774 and 385, 8 687 and 247, 16 693 and 255 (4 without the
 // assignment of tiles to XCDs).  A thread that walks 8 rows of a column instead, 777 and 388.
+// A grid of fewer than four rows takes wider tiles, whose lanes would else have no cell in seven of eight:
+// 262144 x 1 cells of 4, 9, 16 and 20 species, us a step, 8 columns 242, 474, 1043 and 978 (which is also
+// 32 lanes a cell, more threads from 2^27 cells on than a grid holds), 32 columns 113, 195, 403 and 394.
 constexpr int kTileLog = 3;
 
 // One stage, its input's primitives in Win and its output's to Wout (PRIM).
@@ -888,8 +892,9 @@ template <int N, int NW, bool PRIM>
 void launch_stage(const WaveTables &t, const Grid &g, bool along_x, const double *Q0, const double *Q, double *Qout,
                   const double *Win, double *Wout, double *T, double r, double a0, double a1, hipStream_t s)
 {
-    int lw = 0;
-    while (lw < kTileLog && (1 << lw) < g.nx) ++lw;
+    int widest = kTileLog, lw = 0;
+    while (widest < 5 && (64 >> (widest + 1)) > g.ny) ++widest;
+    while (lw < widest && (1 << lw) < g.nx) ++lw;
     const int height = 64 >> lw;
     const long long waves = along_x ? ((long long)(g.nx + 1) * g.ny + 62) / 63
                                     : (long long)((g.nx + (1 << lw) - 1) >> lw) * ((g.ny + height - 2) / (height - 1));
