@@ -149,68 +149,64 @@ __global__ void __launch_bounds__(kOrderThreads) order_scatter_kernel(const int 
 // a cell then needs grow by some 35 for four octaves; the rank correlation of p with them is 0.95 to 0.98 (36
 // and 100 species, dt = 1e-8 to 1e-6 s), the temperature's own 0.88 to 0.91.  With
 // de = sum_r q_r (sum_s nu_sr (h_s - 1)) R T / rho, dT/dt = -de / c_v: one pass over the reactions, without the
-// Jacobian.  At most kKeyBlocks wavefronts, which take further cells in turns: one for each of 2^26 cells
-// would be more threads than a grid holds.
-constexpr long long kKeyBlocks = 1 << 20;
-
+// Jacobian.
 __global__ void __launch_bounds__(64) cost_key_kernel(WaveTables t, const double *rhos, const double *Ts, const double *Y,
-                                                      long long n, double dt, int *key)
+                                                      long long n, long long first, double dt, int *key)
 {
     extern __shared__ double sm[];
     const int ns = t.ns, lane = threadIdx.x;
+    const long long cell = first + blockIdx.x;
+    if (cell >= n) return;
     double *c = sm, *g = sm + ns, *hh = sm + 2 * ns, *Mc = sm + 3 * ns;
-    for (long long cell = blockIdx.x; cell < n; cell += gridDim.x) {
-        const double rho = rhos[cell], T = Ts[cell];
-        bool fin = rho > 0.0 && __builtin_isfinite(rho) && T >= kTmin && T <= kTmax;
-        const double iT = 1.0 / T, lT = log(T), rc = 1e-3 * rho, lPaRT = t.lnPaR - lT;
-        double cv = 0.0;
-        for (int s = lane; s < ns; s += kW) {
-            const double y = Y[(size_t)s * n + cell], im = 1.0 / t.M[s];
-            fin = fin && __builtin_isfinite(y);
-            const double *a = t.nasa + 14 * s + (T < t.Tmid[s] ? 0 : 7);
-            const double cp = fma(T, fma(T, fma(T, fma(T, a[4], a[3]), a[2]), a[1]), a[0]);
-            const double h = fma(a[5], iT, fma(T, fma(T, fma(T, fma(T, a[4] * 0.2, a[3] * 0.25), a[2] * (1.0 / 3.0)), a[1] * 0.5), a[0]));
-            const double e = fma(a[0], lT, fma(T, fma(T, fma(T, fma(T, a[4] * 0.25, a[3] * (1.0 / 3.0)), a[2] * 0.5), a[1]), a[6]));
-            c[s] = y * (rc * im);
-            g[s] = h - e;
-            hh[s] = h;
-            cv = fma(y * im, cp - 1.0, cv);
-        }
-        wave_sync();
-        for (int q = lane; q < t.ntb; q += kW) {
-            double acc = 0.0;
-#pragma unroll 8
-            for (int s = 0; s < ns; ++s) acc = fma(t.effT[(size_t)s * t.ntb + q], c[s], acc);
-            Mc[q] = acc;
-        }
-        wave_sync();
-        const double4 *rxd4 = reinterpret_cast<const double4 *>(t.rxd);
-        double de = 0.0;
-        for (int r = lane; r < t.nr; r += kW) {
-            const RxnRec x = t.rxc[r];
-            const double4 rd = rxd4[r];   // ln A, b, Ta, sum nu
-            double p[2] = {1.0, 1.0}, sg = 0.0, sh = 0.0;
-#pragma unroll
-            for (int q = 0; q < 6; ++q) {
-                const int s = x.coff[q] / 8, nu = x.nu[q], m = nu < 0 ? -nu : nu;
-                sg = fma((double)nu, g[s], sg);
-                sh = fma((double)nu, hh[s], sh);
-                for (int k = 0; k < m; ++k) p[q / 3] *= c[s];
-            }
-            const double lkf = fma(-rd.z, iT, fma(rd.y, lT, rd.x));
-            const double pf = exp(lkf) * p[0], pb = x.rev ? exp(lkf - (rd.w * lPaRT - sg)) * p[1] : 0.0;
-            de = fma((x.tb >= 0 ? Mc[x.tb] : 1.0) * (pf - pb), sh - rd.w, de);
-        }
-        const double P = fabs(wave_sum(de)) * dt / (rc * wave_sum(cv));   // |dT/dt| dt / T: R T cancels
-        const bool ok = __all(fin);
-        int k = 0;
-        if (ok) {
-            if (!(P < 1e9)) k = kC - 1;
-            else if (P > 0.0) k = min(max((int)floor(0.25 * log2(P)) + 2, 0), kC - 1);
-        }
-        if (lane == 0) key[cell] = k;
-        wave_sync();   // the next cell writes over what this one read
+    const double rho = rhos[cell], T = Ts[cell];
+    bool fin = rho > 0.0 && __builtin_isfinite(rho) && T >= kTmin && T <= kTmax;
+    const double iT = 1.0 / T, lT = log(T), rc = 1e-3 * rho, lPaRT = t.lnPaR - lT;
+    double cv = 0.0;
+    for (int s = lane; s < ns; s += kW) {
+        const double y = Y[(size_t)s * n + cell], im = 1.0 / t.M[s];
+        fin = fin && __builtin_isfinite(y);
+        const double *a = t.nasa + 14 * s + (T < t.Tmid[s] ? 0 : 7);
+        const double cp = fma(T, fma(T, fma(T, fma(T, a[4], a[3]), a[2]), a[1]), a[0]);
+        const double h = fma(a[5], iT, fma(T, fma(T, fma(T, fma(T, a[4] * 0.2, a[3] * 0.25), a[2] * (1.0 / 3.0)), a[1] * 0.5), a[0]));
+        const double e = fma(a[0], lT, fma(T, fma(T, fma(T, fma(T, a[4] * 0.25, a[3] * (1.0 / 3.0)), a[2] * 0.5), a[1]), a[6]));
+        c[s] = y * (rc * im);
+        g[s] = h - e;
+        hh[s] = h;
+        cv = fma(y * im, cp - 1.0, cv);
     }
+    wave_sync();
+    for (int q = lane; q < t.ntb; q += kW) {
+        double acc = 0.0;
+#pragma unroll 8
+        for (int s = 0; s < ns; ++s) acc = fma(t.effT[(size_t)s * t.ntb + q], c[s], acc);
+        Mc[q] = acc;
+    }
+    wave_sync();
+    const double4 *rxd4 = reinterpret_cast<const double4 *>(t.rxd);
+    double de = 0.0;
+    for (int r = lane; r < t.nr; r += kW) {
+        const RxnRec x = t.rxc[r];
+        const double4 rd = rxd4[r];   // ln A, b, Ta, sum nu
+        double p[2] = {1.0, 1.0}, sg = 0.0, sh = 0.0;
+#pragma unroll
+        for (int q = 0; q < 6; ++q) {
+            const int s = x.coff[q] / 8, nu = x.nu[q], m = nu < 0 ? -nu : nu;
+            sg = fma((double)nu, g[s], sg);
+            sh = fma((double)nu, hh[s], sh);
+            for (int k = 0; k < m; ++k) p[q / 3] *= c[s];
+        }
+        const double lkf = fma(-rd.z, iT, fma(rd.y, lT, rd.x));
+        const double pf = exp(lkf) * p[0], pb = x.rev ? exp(lkf - (rd.w * lPaRT - sg)) * p[1] : 0.0;
+        de = fma((x.tb >= 0 ? Mc[x.tb] : 1.0) * (pf - pb), sh - rd.w, de);
+    }
+    const double P = fabs(wave_sum(de)) * dt / (rc * wave_sum(cv));   // |dT/dt| dt / T: R T cancels
+    const bool ok = __all(fin);
+    int k = 0;
+    if (ok) {
+        if (!(P < 1e9)) k = kC - 1;
+        else if (P > 0.0) k = min(max((int)floor(0.25 * log2(P)) + 2, 0), kC - 1);
+    }
+    if (lane == 0) key[cell] = k;
 }
 
 }  // namespace
@@ -218,9 +214,15 @@ __global__ void __launch_bounds__(64) cost_key_kernel(WaveTables t, const double
 hipError_t launch_cost_key(const WaveTables &t, const Arena &a, long long n, double dt, int *key, hipStream_t s)
 {
     const size_t lds = sizeof(double) * (size_t)(3 * t.ns + t.ntb);
-    const dim3 grid((unsigned)(n < kKeyBlocks ? n : kKeyBlocks));
-    hipLaunchKernelGGL(cost_key_kernel, grid, dim3(64), lds, s, t, a.rho, a.T, a.Y, n, dt, key);
-    return hipGetLastError();
+    // a grid holds less than 2^32 threads, so the cells go in parts of half as many
+    constexpr long long kPart = (1ll << 31) / kW;
+    for (long long first = 0; first < n; first += kPart) {
+        const long long m = n - first < kPart ? n - first : kPart;
+        hipLaunchKernelGGL(cost_key_kernel, dim3((unsigned)m), dim3(kW), lds, s, t, a.rho, a.T, a.Y, n, first, dt, key);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_cost_order(const int *key, long long n, bool direct, int *order, int *ocount,
