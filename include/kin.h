@@ -192,12 +192,14 @@ kin_status kin_state_reset(kin_ctx *ctx, int32_t inst_id, const double *rho, con
  * are replaced by the step's result (a failed cell keeps its state) and its status, level
  * (deepest halving level) and iters (Newton iterations including failed tries) are written.
  * s may be NULL for the defaults.  With n > 1 all instances go out in one graph launch.
- * A single instance of at least 262144 cells in the lane layout, or 32768 in the others
- * (about four times the cells a layout keeps in flight), takes its cells in cost order.  When
- * its iters come from an advance of its current state (no kin_state_reset or conserved
- * reset since), the classes are the iterations each cell needed: 320 or more first, then
- * 160-319, 80-159, 40-79, 20-39, 10-19, 5-9 and the rest.  Otherwise, in the lane layout,
- * they are the octave of the temperature change the source term predicts over dt.  Each class
+ * A single instance that is large enough takes its cells in cost order.  When its iters come
+ * from an advance of its current state (no kin_state_reset or conserved reset since), the
+ * classes are the iterations each cell needed: 320 or more first, then 160-319, 80-159, 40-79,
+ * 20-39, 10-19, 5-9 and the rest; otherwise they come from the temperature change that the
+ * source term predicts over dt, an octave a class in the lane layout, four in the others.  Large
+ * enough is 262144 cells in the lane layout (about four times the cells it keeps in flight); 513
+ * with a workgroup per cell; with a wavefront per cell 8192 by iterations, and by the prediction
+ * 2560, or 4096 below 32 species.  Never with point_implicit.  Each class
  * keeps index order.  This shortens the launch's tail; every cell's result is bitwise the
  * same in any order.  Advances of one instance must be ordered on one stream (or
  * synchronised), as the order is computed on `stream` from the previous advance's iters.

@@ -12,7 +12,8 @@
 //
 // A stable counting sort in three kernels over tiles of kOrderTile cells: per-tile class
 // counts, one block that turns them into each tile's first position per class, and a scatter
-// that ranks a tile's cells within their class by wavefront ballots.
+// that ranks a tile's cells within their class by wavefront ballots.  Up to kOrderSmall cells one block
+// does it all: there a launch that orders is short enough to feel two launches more.
 #include <hip/hip_runtime.h>
 
 #include "kin_internal.h"
@@ -143,6 +144,69 @@ __global__ void __launch_bounds__(kOrderThreads) order_scatter_kernel(const int 
     }
 }
 
+// The same of at most kOrderSmall cells in one block: a thread counts the classes of its run of cells, 16 bits
+// a class, the block scans the counts, and every cell takes its place.  A first advance of inert cells of 36
+// species, us in index order, with three kernels and with this one: 2560 cells 199, 224 and 207; 4096 cells
+// 294, 316 and 304; 8192 cells 462, 495 and 482 (32768 cells in one block: 1600 with three, 1638 with one).
+constexpr int kSmallRun = 8, kOrderSmall = kSmallRun * kScanThreads;
+
+__global__ void __launch_bounds__(kScanThreads) order_small_kernel(const int *iters, int n, int direct, int *order,
+                                                                   unsigned long long *clear)
+{
+    static_assert(kC == 8 && kOrderSmall < 65536, "two words of four 16-bit counts");
+    constexpr int kWaves = kScanThreads / 64;
+    __shared__ unsigned long long part[kWaves][2];
+    const int u = threadIdx.x, lane = u & 63, w = u >> 6;
+    if (clear && u == 0) *clear = 0ull;   // the advance's work counter
+    const int per = (n + kScanThreads - 1) / kScanThreads;
+    const int a = min(u * per, n), b = min(a + per, n);
+    int f[kSmallRun];   // 0..7 are the classes kC - 1..0, in the order of their places
+#pragma unroll
+    for (int j = 0; j < kSmallRun; ++j) f[j] = a + j < b ? kC - 1 - cost_class(iters[a + j], direct) : 0;
+    unsigned long long own[2] = {0, 0}, sum[2];
+#pragma unroll
+    for (int j = 0; j < kSmallRun; ++j) {
+        const unsigned long long one = a + j < b ? 1ull << (16 * (f[j] & 3)) : 0;
+        own[0] += f[j] < 4 ? one : 0;
+        own[1] += f[j] < 4 ? 0 : one;
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        sum[q] = own[q];
+        for (int d = 1; d < 64; d <<= 1) {
+            const unsigned long long v = __shfl_up(sum[q], d);
+            if (lane >= d) sum[q] += v;
+        }
+        if (lane == 63) part[w][q] = sum[q];
+    }
+    __syncthreads();
+    unsigned long long all[2] = {0, 0}, next[2] = {sum[0] - own[0], sum[1] - own[1]};
+#pragma unroll
+    for (int k = 0; k < kWaves; ++k)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const unsigned long long v = part[k][q];
+            next[q] += k < w ? v : 0;
+            all[q] += v;
+        }
+    // next: cells of each class in the threads before this one; with the classes before it, the next place
+    unsigned long long at = 0;
+#pragma unroll
+    for (int c = 0; c < kC; ++c) {
+        next[c >> 2] += at << (16 * (c & 3));
+        at += all[c >> 2] >> (16 * (c & 3)) & 0xffff;
+    }
+#pragma unroll
+    for (int j = 0; j < kSmallRun; ++j)
+        if (a + j < b) {
+            const int sh = 16 * (f[j] & 3);
+            const int p = (int)((f[j] < 4 ? next[0] : next[1]) >> sh & 0xffff);
+            if (f[j] < 4) next[0] += 1ull << sh;
+            else next[1] += 1ull << sh;
+            if (p < n) order[p] = a + j;
+        }
+}
+
 // Cost class of each cell for a first advance, one wavefront per cell, by the relative temperature change
 // that the source term predicts over dt, p = |dT/dt| dt / T: a class takes four octaves of p, from 0 below
 // 1 / 16 (and cells that the advance refuses) to 7 above 2^20 (and where p is no number).  The iterations that
@@ -232,6 +296,10 @@ hipError_t launch_cost_order(const int *key, long long n, bool direct, int *orde
     if (n > 0x7fffffffLL) return hipErrorInvalidValue;
     const long long tiles = order_tiles(n);
     const int d = direct ? 1 : 0;
+    if (n <= kOrderSmall) {
+        hipLaunchKernelGGL(order_small_kernel, dim3(1), dim3(kScanThreads), 0, s, key, (int)n, d, order, clear);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(order_count_kernel, dim3((unsigned)tiles), dim3(kOrderThreads), 0, s, key, n, d, ocount);
     hipLaunchKernelGGL(order_scan_kernel, dim3(1), dim3(kScanThreads), 0, s, ocount, tiles, clear);
     hipLaunchKernelGGL(order_scatter_kernel, dim3((unsigned)tiles), dim3(kOrderThreads), 0, s, key, n, d, ocount,

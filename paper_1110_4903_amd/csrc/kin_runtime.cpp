@@ -57,14 +57,22 @@ struct Inst {
     bool iters_current = false;  // iters[] holds the counts of an advance of the current state
 };
 
-// Instances at least this large take their cells in cost order: about four times the cells
-// the lane layout keeps in flight (65536 lanes; the order also moves cells apart that share cache
-// lines), more than are in flight in the others (about 2500 wavefronts, 512 workgroups); below that
-// every cell starts at once and the order only costs its 0.06 to 0.08 ms.  In index order and in this, ms:
-// 36 species, 2700 cells 16.8 and 15.5, 3200 cells 16.8 and 14.5, 16384 cells (0.1 us) 38.0 and 31.7; 100 species,
-// 520 cells 23.2 and 22.5, 768 cells 32.3 and 22.5, 2048 cells 57 and 47.
+// Instances at least this large take their cells in cost order: about four times the cells that the
+// lane layout keeps in flight (65536 lanes; the order also moves cells apart that share cache lines),
+// more than are in flight in the others: 512 workgroups; some 2500 wavefronts from 32 species on, by their LDS;
+// 3072 below, by their registers (with 4096 cells a quarter waits).  Below that every cell starts at once.  First advances of unequal cells, in index order and in this, ms: 36 species, 2700 cells 16.8
+// and 15.5, 3200 cells 16.8 and 14.5, 16384 cells (0.1 us) 38.0 and 31.7; 20 species, 6000 cells
+// (0.01 us) 7.2 and 5.4; 100 species, 520 cells 23.2 and 22.5, 768 cells 32.3 and 22.5, 2048 cells 57 and 47.
+// Cells that all need one to three iterations pay for it, us: 36 species, 4096 cells 296 to 317 and 304 to
+// 331, 16384 cells 810 to 1262 and 845 to 1288; 20 species, 4096 cells 88 to 207 and 95 to 213, 16384 cells 231
+// to 587 and 262 to 621.
+// By the counts of an advance before (kOrderMinCounted) the wavefronts' layouts gain only where the cells
+// that were expensive stay so: 36 species, second and third advance, index order against this: 24000 cells at
+// 1 us 1.07 and 1.10, 32767 cells in FP32-LU 1.45 and 1.43, 8192 to 16384 cells 0.92 to 1.14, 4096 cells at
+// 0.01 us 0.80 and 0.98.
 constexpr long long kOrderMinLaneCells = 262144;
-constexpr long long kOrderMinCells = 2560;
+constexpr long long kOrderMinCells = 2560, kOrderMinCellsSmall = 4096, kOrderMinCounted = 8192;
+constexpr int kOrderNs = 32;   // species from which on kOrderMinCells holds, kOrderMinCellsSmall below
 constexpr long long kOrderMinBlockCells = 513;
 
 // Code objects already compiled in this process, keyed by their source.
@@ -1394,6 +1402,8 @@ kin_status kin_advance(kin_ctx *ctx, const int32_t *inst_ids, const double *dts,
     // order's scan also clears the work counter; without an order a kernel of its own does
     const long long order_min = layout == KIN_LAYOUT_LANE    ? kOrderMinLaneCells
                                 : uses_block(m, layout, prec) ? kOrderMinBlockCells
+                                : in.iters_current            ? kOrderMinCounted
+                                : m.h.ns < kOrderNs           ? kOrderMinCellsSmall
                                                               : kOrderMinCells;
     if (!o.point_implicit && in.n >= order_min && in.n <= 0x7fffffffLL) {
         const Arena ar = arena_at(static_cast<char *>(in.buf), in.n, m.h.ns);
