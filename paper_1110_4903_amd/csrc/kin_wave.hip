@@ -254,7 +254,8 @@ __device__ __forceinline__ void reaction_terms(const WaveTables &t, const Lds &L
 
 // f = dx/dt and J = df/dx of the cell at x (lane i holds x_i).  Leaves J in L.J (row-major,
 // stride NPAD, zero beyond column N - 1) and f in L.W.
-template <int NPAD, bool PK>
+// DEEP: more loads in flight in the sums over the species.
+template <int NPAD, bool PK, bool DEEP>
 __device__ __forceinline__ void eval(const WaveTables &t, const Lds &L, int lane, double rho, double xs,
                                      double Ms, double invMs)
 {
@@ -286,7 +287,7 @@ __device__ __forceinline__ void eval(const WaveTables &t, const Lds &L, int lane
     for (int r = lane; r < t.ntb; r += kW) {
         double acc = 0.0;
         const double *e = t.effT + r;
-#pragma unroll 12
+#pragma unroll (DEEP ? 12 : 4)
         for (int s = 0; s < ns; ++s, e += t.ntb) acc = fma(*e, L.c[s * VS], acc);
         L.Mc[r] = acc;
     }
@@ -389,11 +390,11 @@ __device__ __forceinline__ void eval(const WaveTables &t, const Lds &L, int lane
     if (lane <= ns) {
         double acc = 0.0;
         if (lane < ns) {
-#pragma unroll 12
+#pragma unroll (DEEP ? 12 : 4)
             for (int s = 0; s < ns; ++s) acc = fma(E[s * VS], L.J[(size_t)s * JS + lane], acc);
             L.J[(size_t)ns * JS + lane] = -fma(fT, cvk, acc) * icv;
         } else {
-#pragma unroll 8
+#pragma unroll (DEEP ? 8 : 4)
             for (int s = 0; s < ns; ++s) acc = fma(CV[s * VS], L.W[s], fma(E[s * VS], L.J[(size_t)s * JS + ns], acc));
             L.J[(size_t)ns * JS + ns] = -fma(fT, dcv, acc) * icv;
             L.W[ns] = fT;
@@ -702,7 +703,10 @@ __device__ __forceinline__ bool substep(const WaveTables &t, const Lds &L, int l
         tz.nasa += z; tz.Tmid += z; tz.rxd += z; tz.rxc += z; tz.rxk += z; tz.effT += z; tz.tbA += z; tz.tbB += z; tz.chunk_rp += z;
         int ln = lane;
         asm volatile("" : "+v"(ln));
-        eval<NPAD, PK>(tz, L, ln, rho, xk, Ms, invMs);
+        // (FP32-LU of 37 to 39 and 45 to 47 species is 4 to 6% slower with the deeper loads: 300 cells of 39 species
+        // 3.25 ms without, 3.46 ms with them; 46 species 5.38 and 5.70 ms)
+        constexpr bool kDeep = !(F32 && !PK && (NPAD == 40 || NPAD == 48));
+        eval<NPAD, PK, kDeep>(tz, L, ln, rho, xk, Ms, invMs);
         bool ok;
         double d;
         if constexpr (F32) {
