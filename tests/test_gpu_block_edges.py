@@ -101,3 +101,36 @@ def test_block_kernel_batch_holds_no_workspace():
         for i in ids[:2]:
             for x, y in zip(c.download(i), want):
                 assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("n", [40, 600])
+def test_block_kernel_in_a_callers_graph(n):
+    """An advance captured by the caller (the launch attribute of the kernel's LDS, the cost order from 513 cells
+    on), replayed with eager work between, is the eager advance."""
+    import torch
+    from paper_1110_4903_amd import kin
+    m = synth.make_mechanism(synth.MechRecipe("cap66", seed=66, n_elements=4, n_species=66, n_reactions=150,
+                                              frac_third_body=0.15, frac_irreversible=0.3))
+    states = [synth.uniform_cells(30 + k, n, m.ns, 0.5) for k in range(3)]
+    with kin.Context(0) as c:
+        mid = c.mech_upload(m)
+        st = states[0]
+        want = []
+        for q in states:
+            j = c.state_upload(mid, q.rho, q.T, q.Y)
+            c.advance([j], [1e-8])
+            want.append(c.download(j)[:5])
+        i = c.state_upload(mid, st.rho, st.T, st.Y)
+        torch.cuda.synchronize()
+        s, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            c.advance([i], [1e-8], stream=s)
+        x = torch.zeros(1 << 20, device="cuda")
+        for q, w in zip(states + states, want + want):
+            c.state_reset(i, q.rho, q.T, q.Y)
+            x.add_(1.0)
+            torch.cuda.synchronize()
+            g.replay()
+            torch.cuda.synchronize()
+            for a, b in zip(c.download(i)[:5], w):
+                assert np.array_equal(a, b)
