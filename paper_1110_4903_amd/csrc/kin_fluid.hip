@@ -14,9 +14,9 @@
 //   update       per cell: the stage's combination of the sweep's start state, the stage state
 //                and dt times the flux difference.
 // One kernel does a stage: a cell's two fluxes, its update and the primitives of its new state stay
-// in registers, and only the step's first primitives have a kernel of their own.  Up to 16 species a
-// lane does all of a face and a cell (fluid_stage_kernel); two wavefronts share them on small grids of
-// nine species and up, four from 17 to 64 species (fluid_wide_kernel).  Larger mixtures, and grids
+// in registers, and only the step's first primitives have a kernel of their own.  Up to 9 species a
+// lane does all of a face and a cell (fluid_stage_kernel); two wavefronts share them from 10 to 16 species
+// (and of 9 on small grids), four from 17 to 64 (fluid_wide_kernel).  Larger mixtures, and grids
 // whose arrays exceed 32-bit offsets, do a stage in two kernels, with the fluxes in memory.
 // Consecutive lanes take consecutive x, so an access of a wavefront is a few contiguous runs of a
 // row.  The six-cell stencil is read from the state and primitive arrays, which neighbouring lanes
@@ -47,10 +47,9 @@ namespace kin {
 namespace {
 
 constexpr double kAlphaMP = 2.0;
-// Mixtures of at most this many species run kernels compiled for their species count: face states
-// and densities stay in registers, and the species loops unroll without a test between them, so the
-// loads of one species are not held back until the previous one is done.  Larger mixtures stream
-// their species (NSR = 0).
+// Up to this many species a wavefront's kernels are compiled for their count (the stages of larger mixtures
+// for a part of it): face states and densities stay in registers, and the species loops unroll without a
+// test between them, so the loads of one species are not held back until the previous one is done.
 constexpr int kFluidNsRegs = 16;
 
 // median(0, a, b): zero when the signs differ, else the argument of smaller magnitude
@@ -841,13 +840,18 @@ __global__ void fluid_energy_back_kernel(Grid g, double *Q, const double *KE, co
     Q[(size_t)(g.ns + 2) * g.n + i] = Es[i] + KE[i];
 }
 
-// f(N, NW): up to kFluidNsRegs species the kernels compiled for N of them (NW = 1), from nine on in small
-// grids those of two wavefronts that take at most N each; up to 64 species those of four; else (or where
-// 32-bit offsets do not reach) N = 0, the streamed kernels.
-// Two wavefronts shorten a face's chain and cost more in all.  Nine species, us a step with one and with two:
-// 3750 cells 54.8 and 47.4, 15000 cells 55.3 and 51.3, 25200 cells 56.6 and 55.6, 51200 cells 60.7 and 66.2,
-// 2^20 cells 701 and 717.
+// f(N, NW): up to kFluidNsOne species the kernels compiled for N of them (NW = 1), then (and for that many in
+// small grids) up to 16 species those of two wavefronts that take at most N each, up to 64 those of four;
+// else (or where 32-bit offsets do not reach) N = 0, the streamed kernels.
+// Two wavefronts shorten a face's chain, and do its scalars twice; from 12 species on a lane that does a face
+// alone leaves one wavefront on a SIMD (256 registers, 13 species).  us a step with one and with two, on
+// 160^2, 512^2 and 1024^2 cells:
+//   9 species  55 and 56, 166 and 175,  635 and 651     13 species  69 and 64, 289 and 220, 1188 and 900
+//  10 species  58 and 56, 179 and 176,  728 and 703     14 species  73 and 64, 305 and 223, 1279 and 930
+//  12 species  65 and 60, 232 and 207,  963 and 824     16 species  79 and 70, 333 and 250, 1404 and 1060
+// Nine species on small grids: 3750 cells 54.8 and 47.4, 15000 cells 55.3 and 51.3, 25200 cells 56.6 and 55.6.
 constexpr long long kFluidSmall = 16384;
+constexpr int kFluidNsOne = 9;
 template <int N = 1, typename Fn>
 void ns_class(const Grid &g, Fn f)
 {
@@ -856,10 +860,12 @@ void ns_class(const Grid &g, Fn f)
         f(integral_constant<int, 0>{}, integral_constant<int, 1>{});
     } else {
         // (four wavefronts are up to 8.2 threads a cell, of which a grid holds less than 2^32)
-        const bool reach = g.n < (1ll << 29), reach4 = g.n < (1ll << 32) / 9, two = g.n <= kFluidSmall && g.ns >= 9 && g.ns <= 16;
-        if (reach && !two && g.ns == N) return f(integral_constant<int, N>{}, integral_constant<int, 1>{});
+        const bool reach = g.n < (1ll << 29), reach4 = g.n < (1ll << 32) / 9;
+        const bool two = g.ns <= 16 && (g.ns > kFluidNsOne || (g.ns == kFluidNsOne && g.n <= kFluidSmall));
+        if constexpr (N <= kFluidNsOne)
+            if (reach && !two && g.ns == N) return f(integral_constant<int, N>{}, integral_constant<int, 1>{});
         if constexpr (N >= 5 && N <= 8)
-            if (two && (g.ns + 1) / 2 == N) return f(integral_constant<int, N>{}, integral_constant<int, 2>{});
+            if (reach && two && (g.ns + 1) / 2 == N) return f(integral_constant<int, N>{}, integral_constant<int, 2>{});
         if constexpr (N >= 5)
             if (reach4 && g.ns > 16 && (g.ns + 3) / 4 == N) return f(integral_constant<int, N>{}, integral_constant<int, 4>{});
         ns_class<N + 1>(g, f);

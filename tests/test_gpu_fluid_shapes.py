@@ -79,3 +79,25 @@ def test_fluid_step_long_single_row():
     scale[ns:ns + 2] = scale[ns:ns + 2].max()
     for v in range(ns + 3):
         assert float((out[v] - Q[v]).abs().max()) <= 1e-12 * scale[v], v
+
+
+@pytest.mark.parametrize("ns", [9, 10, 11, 13, 14, 16])
+@pytest.mark.parametrize("nx,ny", [(128, 128), (201, 97), (20000, 2)])
+def test_fluid_step_two_wavefronts(nx, ny, ns):
+    """The species counts that two wavefronts share (of nine only up to 16384 cells), even and odd, on grids at and
+    beyond that size.  Gate as for the other fluid parity tests."""
+    from oracle import fluid_oracle as fo
+    from paper_1110_4903_amd import kin
+    m = two_range(ns, 7)
+    gas = fo.Gas(m)
+    dx, dy = 1e-3 / nx, 1e-3 / ny
+    Q = np.ascontiguousarray(flow_state(fo, gas, nx, ny, 3, 500.0, 1800.0))
+    with kin.Context(0) as ctx:
+        fid = ctx.fluid_create(ctx.mech_upload(m), nx, ny, dx, dy, 1)
+        ctx.fluid_upload(fid, Q)
+        dt = fo.max_dt(gas, Q, dx, dy, 0.4)
+        for y_first in (False, True):
+            ctx.fluid_step(fid, dt, y_first=y_first)
+            Q = fo.fluid_step(gas, Q, dt, dx, dy, "outflow", y_first=y_first)
+        d = scaled_diff(ctx.fluid_download(fid), Q)
+        assert np.all(d <= 1e-10), d
