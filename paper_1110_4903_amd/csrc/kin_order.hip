@@ -7,8 +7,8 @@
 // geometric classes, most expensive first: >= 320, 160-319, ..., 10-19, 5-9 and < 5
 // iterations.  A first advance (no counts yet) passes classes computed from the source term (direct):
 // by the lane kernels' module in that layout, by cost_key_kernel in the others.  Within a class cells
-// keep their index order, which keeps the state accesses of neighbouring lanes coalesced.  Which cell a lane takes does not change that cell's
-// arithmetic: results are bitwise the same in any order.
+// keep their index order, which keeps the state accesses of neighbouring lanes coalesced.  Which cell a
+// lane takes does not change that cell's arithmetic: results are bitwise the same in any order.
 //
 // A stable counting sort in three kernels over tiles of kOrderTile cells: per-tile class
 // counts, one block that turns them into each tile's first position per class, and a scatter
@@ -56,16 +56,16 @@ __global__ void __launch_bounds__(kOrderThreads) order_count_kernel(const int *i
 }
 
 // In place: ocount[kC t + c] becomes the first position of tile t's class-c cells.  Classes
-// are laid out from kC - 1 down to 0; within a class, tiles in order.  One block; thread u
+// are laid out from kC - 1 down to 0; within a class, tiles in order.  One block of T threads; thread u
 // owns a contiguous run of tiles.
-__global__ void __launch_bounds__(kScanThreads) order_scan_kernel(int *ocount, long long tiles,
-                                                                  unsigned long long *clear)
+template <int T>
+__global__ void __launch_bounds__(T) order_scan_kernel(int *ocount, long long tiles, unsigned long long *clear)
 {
     if (clear && threadIdx.x == 0) *clear = 0ull;  // the advance's work counter
-    __shared__ int sc[kC][kScanThreads];
+    __shared__ int sc[kC][T];
     __shared__ int tot[kC];
     const int u = threadIdx.x;
-    const long long per = (tiles + kScanThreads - 1) / kScanThreads;
+    const long long per = (tiles + T - 1) / T;
     const long long b0 = (long long)u * per, b1 = b0 + per < tiles ? b0 + per : tiles;
     int s[kC];
 #pragma unroll
@@ -77,7 +77,7 @@ __global__ void __launch_bounds__(kScanThreads) order_scan_kernel(int *ocount, l
     for (int c = 0; c < kC; ++c) sc[c][u] = s[c];
     __syncthreads();
     // inclusive scans over the threads (Hillis-Steele)
-    for (int d = 1; d < kScanThreads; d <<= 1) {
+    for (int d = 1; d < T; d <<= 1) {
         int v[kC];
 #pragma unroll
         for (int c = 0; c < kC; ++c) v[c] = u >= d ? sc[c][u - d] : 0;
@@ -86,7 +86,7 @@ __global__ void __launch_bounds__(kScanThreads) order_scan_kernel(int *ocount, l
         for (int c = 0; c < kC; ++c) sc[c][u] += v[c];
         __syncthreads();
     }
-    if (u < kC) tot[u] = sc[u][kScanThreads - 1];
+    if (u < kC) tot[u] = sc[u][T - 1];
     __syncthreads();
     int run[kC];
     int acc = 0;
@@ -147,7 +147,8 @@ __global__ void __launch_bounds__(kOrderThreads) order_scatter_kernel(const int 
 // The same of at most kOrderSmall cells in one block: a thread counts the classes of its run of cells, 16 bits
 // a class, the block scans the counts, and every cell takes its place.  A first advance of inert cells of 36
 // species, us in index order, with three kernels and with this one: 2560 cells 199, 224 and 207; 4096 cells
-// 294, 316 and 304; 8192 cells 462, 495 and 482 (32768 cells in one block: 1600 with three, 1638 with one).
+// 294, 316 and 304; 8192 cells 462, 495 and 482 (32768 cells in one block: 1600 with three, 1638 with one;
+// one wavefront instead of sixteen: 230, 335 and 553).
 constexpr int kSmallRun = 8, kOrderSmall = kSmallRun * kScanThreads;
 
 __global__ void __launch_bounds__(kScanThreads) order_small_kernel(const int *iters, int n, int direct, int *order,
@@ -301,7 +302,11 @@ hipError_t launch_cost_order(const int *key, long long n, bool direct, int *orde
         return hipGetLastError();
     }
     hipLaunchKernelGGL(order_count_kernel, dim3((unsigned)tiles), dim3(kOrderThreads), 0, s, key, n, d, ocount);
-    hipLaunchKernelGGL(order_scan_kernel, dim3(1), dim3(kScanThreads), 0, s, ocount, tiles, clear);
+    // One wavefront where a lane has a tile at most: on a device that other streams keep full it starts as
+    // soon as any wavefront of theirs ends, a block of sixteen when a compute unit has run empty (serving 160
+    // requests, mean time in the queue and running: 0.05 to 0.1 ms, and 3 ms).
+    if (tiles <= 64) hipLaunchKernelGGL(order_scan_kernel<64>, dim3(1), dim3(64), 0, s, ocount, tiles, clear);
+    else hipLaunchKernelGGL(order_scan_kernel<kScanThreads>, dim3(1), dim3(kScanThreads), 0, s, ocount, tiles, clear);
     hipLaunchKernelGGL(order_scatter_kernel, dim3((unsigned)tiles), dim3(kOrderThreads), 0, s, key, n, d, ocount,
                        order);
     return hipGetLastError();
