@@ -250,11 +250,11 @@ def run_conserved_adapter(torch, ctx, kin, synth, args, stream):
 
 
 def run_global_tier(torch, ctx, kin, flops, synth, args, stream):
-    """The global-memory layout (one wavefront per cell, the cell's matrix in HBM, as in the
-    paper's first kinetics kernel) on a generated 100-species / 600-reaction mechanism, beyond the
-    wave layout's 63 species: one FP64 step of 1e-6 s on 65536 cells (Dirichlet(0.5), seed 7).
-    Achieved bandwidth = the algorithmic bytes of a Newton iteration (flops.global_tier_bytes)
-    times the iterations of the launch, over its duration."""
+    """The global layout's FP64 form of 64 to 126 species (a workgroup per cell, the matrix in its
+    registers) on a generated 100-species / 600-reaction mechanism, beyond the wave layout's 63
+    species: one step of 1e-6 s on 65536 cells (Dirichlet(0.5), seed 7).  Achieved rate = the
+    operations of a Newton iteration (flops.newton_iteration_flops) times the iterations of the
+    launch, over its duration; no matrix goes through HBM."""
     n = 4096 if args.quick else 65536
     m = synth.make_mechanism(synth.MechRecipe("gen100", seed=1100, n_elements=5, n_species=100,
                                               n_reactions=600, frac_third_body=0.15,
@@ -263,7 +263,7 @@ def run_global_tier(torch, ctx, kin, flops, synth, args, stream):
     st = device_state(torch, synth.uniform_cells(7, n, m.ns, 0.5))
     warm = device_state(torch, synth.uniform_cells(8, 1024, m.ns, 0.5))
     wid = ctx.state_upload(mid, warm["rho"], warm["T"], warm["Y"], stream=stream)
-    ctx.advance([wid], [0.0], stream=stream)  # a zero step (one iteration) sets up the workspace pool
+    ctx.advance([wid], [0.0], stream=stream)  # a zero step (one iteration) loads the kernels
     iid = ctx.state_upload(mid, st["rho"], st["T"], st["Y"], stream=stream)
     torch.cuda.synchronize()
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
@@ -274,12 +274,12 @@ def run_global_tier(torch, ctx, kin, flops, synth, args, stream):
     sec = e0.elapsed_time(e1) * 1e-3
     out = ctx.download(iid)
     iters = float(out[4].astype(np.float64).sum())
-    b = flops.global_tier_bytes(m)
-    gbs = b["total"] * iters / sec / 1e9
+    f = flops.newton_iteration_flops(m)["total"]
+    tf = f * iters / sec / 1e12
     res = dict(mechanism="generated 100 species / 600 reactions", cells=n, seconds=sec, cells_per_s=n / sec,
                newton_iters_per_cell=iters / n, status_hist=np.bincount(out[2], minlength=4).tolist(),
-               layout=ctx.query_int(kin.Q_LAYOUT, mid), bytes_per_iteration=b["total"],
-               achieved_GB_s=gbs, hbm_peak_GB_s=8000.0, frac=gbs / 8000.0)
+               layout=ctx.query_int(kin.Q_LAYOUT, mid), flops_per_iteration=f,
+               achieved_TFLOP_s=tf, fp64_peak_TFLOP_s=FP64_PEAK_TFLOPS, frac=tf / FP64_PEAK_TFLOPS)
     for i in (wid, iid):
         ctx.instance_release(i)
     ctx.mech_release(mid)
