@@ -29,7 +29,8 @@
 // memory 127 ms.
 // Measured and not taken: panels of four columns per barrier (5500 cycles a panel: the wavefront that has
 // factored one has its other columns still to do), pivot rows through LDS instead of v_readlane_b32 (LDS
-// bound), four wavefronts, a block of 256 registers a lane alone on its compute unit.
+// bound), four wavefronts, a block of 256 registers a lane alone on its compute unit.  Of 128 registers a lane
+// the compiler spills 31 more (104 bytes of scratch; 21 and 64 below 95 species).
 //
 // Method as in the other layouts: Newton iterations on backward Euler in x = (Y, T) for a
 // constant-(rho, e) cell, (I - hJ) dx = -G, dyadic sub-step halving on failure (Sec. 3.2, Eq.
@@ -421,7 +422,9 @@ __device__ __forceinline__ void b_system(const WaveTables &t, const BlockTables 
 // Gauss-Jordan elimination of A; afterwards column N, the first of its wavefront, holds u_kk x_k in the row
 // that was pivot k.
 // The pivot of a column is the largest entry by the leading 32 bits of its magnitude (exponent and 20
-// bits): a multiplier is then at most 1 + 2^-20, and the search is one 32-bit reduction.
+// bits): a multiplier is then at most 1 + 2^-20, and the search is one 32-bit reduction.  The error of the
+// solution, against LU with pivots by all bits (101 unknowns): Newton matrices of condition up to 1e19, median
+// 1.8e-9 to 2.6e-8 and 1.5e-9 to 7.5e-8; graded random matrices 3.0e-12 and 2.5e-12.
 template <int NC>
 __device__ __forceinline__ void b_eliminate(const BLds &L, int N, int lane, int wid, double (&A)[RW][NC])
 {

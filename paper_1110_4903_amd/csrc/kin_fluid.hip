@@ -22,12 +22,13 @@
 // row.  The six-cell stencil is read from the state and primitive arrays, which neighbouring lanes
 // share through the caches.
 //
-// What bounds it: a stage of nine species on 1024 x 1024 cells takes 107 us along x and 127 us along
-// y, where its 352 bytes a cell at the rate of a large copy (4.7 TB/s) would take 79 us; two
-// wavefronts per SIMD (208 registers: the six-cell loads of nine species in flight) hide the rest of
-// the latency incompletely, and a bound on the registers makes the compiler spill (three wavefronts:
-// 1.8 times the time).  36 species on 401 x 250 cells: 36 and 42 us, of 34 us of traffic that the
-// caches partly hold.  3750 cells of nine species: 7 us a stage, the latency of one wavefront.
+// What bounds it: a stage of nine species on 1024 x 1024 cells takes 102 us along x and 120 us along
+// y, where its 352 bytes a cell at the rate of a large copy (4.7 TB/s) would take 79 us.  A wavefront
+// waits for loads in 30% of its cycles and for an instruction to issue in 40%, with the VALU active in a
+// third of the SIMDs' cycles: too few wavefronts to cover either wait (208 registers, two on a SIMD at
+// most, 1.5 on average), and a bound on the registers makes the compiler spill (three wavefronts: 1.8
+// times the time).  36 species on 401 x 250 cells: 36 and 41 us, of 34 us of traffic that the caches partly
+// hold (waits 30% and 40%, VALU 43%).  3750 cells of nine species: 7 us a stage, one wavefront's latency.
 // us a step, 1024 x 1024 of 9 / 75 x 50 of 9 / 401 x 250 of 36 species:
 //   1166 / 162 / 1111  a division and branches in each limiter, a selection of every coefficient per
 //                      lane, energies summed species by species
@@ -35,7 +36,8 @@
 //                      73-100 us on the large grid)
 //    777 /  67 /  468  one kernel a stage up to 16 species, along y a walk up the columns
 //    687 /  57 /  247  tiles along y, tiles to XCDs in contiguous parts, the wide form
-//    687 /  50 /  247  the wide form of two wavefronts on small grids
+//    687 /  50 /  240  the wide form of two wavefronts on small grids
+//    689 /  50 /  229  lanes without a cell read nothing
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -924,7 +926,6 @@ hipError_t launch_fluid_step(const WaveTables &t, const FluidGrid &fg, double dt
 {
     const Grid g{t.ns, fg.nx, fg.ny, fg.bc, (long long)fg.nx * fg.ny};
     const int block = 256;
-    const unsigned gc = (unsigned)((g.n + block - 1) / block);
     // (a0, a1, stage input, stage output): Q1 = Q + dt L(Q); Q2 = 3/4 Q + 1/4 (Q1 + dt L(Q1));
     // Q <- 1/3 Q + 2/3 (Q2 + dt L(Q2))
     const double a0[3] = {0.0, 0.75, 1.0 / 3.0}, a1[3] = {1.0, 0.25, 2.0 / 3.0};
@@ -948,6 +949,7 @@ hipError_t launch_fluid_step(const WaveTables &t, const FluidGrid &fg, double dt
         } else {
             // a stage is its faces' kernel, then the update's, which but for the step's last also forms the
             // primitives of its output
+            const unsigned gc = (unsigned)((g.n + block - 1) / block);
             auto sweep = [&](auto dirc, bool last_sweep) {
                 constexpr int D = decltype(dirc)::value;
                 const long long nf = D == 0 ? (long long)(g.nx + 1) * g.ny : (long long)g.nx * (g.ny + 1);
@@ -977,8 +979,6 @@ hipError_t launch_fluid_speed(const WaveTables &t, const FluidGrid &fg, const do
                               double dx, double dy, unsigned long long *out, hipStream_t s)
 {
     const Grid g{t.ns, fg.nx, fg.ny, fg.bc, (long long)fg.nx * fg.ny};
-    const int block = 256;
-    const unsigned gc = (unsigned)((g.n + block - 1) / block);
     launch_prim(t, g, Q, W, T, s);
     const long long sb = (g.n + kSpeedThreads - 1) / kSpeedThreads;
     hipLaunchKernelGGL(fluid_speed_kernel, dim3((unsigned)(sb < kSpeedBlocks ? sb : kSpeedBlocks)), dim3(kSpeedThreads),

@@ -282,13 +282,13 @@ hipError_t launch_block(const WaveTables &t, const BlockTables &b, const Advance
 // Global-memory layout (kin_global.hip): workspace doubles per slot, and the launch over
 // `slots` threads with a workspace of slots * global_work_doubles_per_slot doubles.
 size_t global_work_doubles_per_slot(int ns, int ntb);
-// Cost order of an instance's n cells (kin_order.hip): order[n], per-tile scratch
-// ocount[kOrderClasses * order_tiles(n)].  key: the iterations of the previous advance, or
-// with direct, cost classes 0..kOrderClasses-1 already.
-// clear (may be null): a work counter that the order's scan sets to zero on the way
-// Cost classes of n cells (at most 2^31 - 1) for a first advance of dt in the table-driven layouts (3 ns + ntb
+// Cost classes of n cells for a first advance of dt in the table-driven layouts (kin_order.hip; 3 ns + ntb
 // doubles of LDS).
 hipError_t launch_cost_key(const WaveTables &t, const Arena &a, long long n, double dt, int *key, hipStream_t s);
+// Cost order of an instance's n cells (at most 2^31 - 1): order[n], per-tile scratch
+// ocount[kOrderClasses * order_tiles(n)].  key: the iterations of the previous advance, or
+// with direct, cost classes 0..kOrderClasses-1 already.
+// clear (may be null): a work counter that the order sets to zero on the way
 hipError_t launch_cost_order(const int *key, long long n, bool direct, int *order, int *ocount,
                               unsigned long long *clear, hipStream_t s);
 hipError_t launch_global(const WaveTables &t, const AdvanceArgs &a, bool fp32_lu, double *work,

@@ -696,7 +696,7 @@ __device__ __forceinline__ bool substep(const WaveTables &t, const Lds &L, int l
         // Addresses and table entries that an iteration shares with the next are formed again (the zero and
         // the lane come from where the compiler does not see them): hoisted out of the loops they are spilled,
         // and each is read back from memory in every iteration.  With deeper loads in the sums over the
-        // species: 1000 cells of 36 species 14.9 to 14.5 ms, 16384 cells 38.5 to 37.9 ms.
+        // species: 1000 cells of 36 species 12.8 to 12.5 ms, 16384 cells (in index order) 38.5 to 37.9 ms.
         size_t z = 0;
         asm volatile("" : "+s"(z));
         WaveTables tz = t;
